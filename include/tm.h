@@ -332,19 +332,23 @@ int tm_force(tm_ctx *ctx, void *F_dev, int force_prec, const void *X_e, const tm
              int prec, int pc, double coeff, int accumulate, void *G_dev);
 
 /* Autotuner: 1 enables the timing-based choice of the hop launch per kernel
- * variant and shape -- right-hand sides per thread (1, 2 or 4 where they
- * divide every problem's count; one flavour, 12-real links), block size,
- * link-load policy, cap of resident waves per SIMD, LDS staging (FP32 one
- * flavour), then the four fastest of those in each depth of the brick site
- * order, then the three best of those with their single-use streams (output
- * stores; with the xpay operand and / or the time-neighbour loads) accessed
- * non-temporally -- cached per
- * context and persisted to $TM_TUNE_CACHE if set; 0 disables (defaults are
- * then used).
- * Read at context creation, for experiments: TM_HOP_NR, TM_HOP_BS,
+ * variant and shape -- the direction-split kernel (a wave per hop of 64 sites;
+ * several right-hand sides per block with 12-real links in FP32 / FP64), or one
+ * thread per site with 1 or 2 right-hand sides (half precision, one flavour,
+ * 12-real links), block size, link-load policy, cap of resident waves per SIMD
+ * and LDS staging (FP32 one flavour), then the four fastest of those in each
+ * depth of the brick site order, then the three best of those with their
+ * single-use streams (output stores; with the xpay operand and / or the
+ * time-neighbour loads) accessed non-temporally -- cached per context and
+ * persisted to $TM_TUNE_CACHE if set; 0 disables (a rule on sizes and
+ * precision is then used).
+ * Read at context creation, for experiments: TM_HOP_SPLIT (1 / 0: the
+ * direction-split kernel wherever it exists / nowhere), TM_HOP_NR, TM_HOP_BS,
  * TM_LINK_NT, TM_HOP_WCAP, TM_HOP_ZC, TM_HOP_LDS, TM_HOP_NT (mask: 1 output,
- * 2 xpay operand, 4 time neighbours) fix one of those choices,
- * TM_XCD_REMAP=0 turns off the XCD-aware block order.                         */
+ * 2 xpay operand, 4 time neighbours) fix one of those choices (without
+ * TM_HOP_SPLIT=1 on the one-thread kernel; with it TM_HOP_NR counts the
+ * right-hand sides per block), TM_XCD_REMAP=0 turns off the XCD-aware block
+ * order.                                                      */
 int tm_set_tuning(tm_ctx *ctx, int enable);
 
 /* Launch planner of the hop kernel (host arithmetic only: no device work,

@@ -58,10 +58,12 @@ struct tm_ctx {
     int force_zc = -1;                 // TM_HOP_ZC: fixed brick depth of the site order (0: lexicographic)
     int force_wcap = -1;               // TM_HOP_WCAP: fixed cap of resident waves per SIMD (0: none)
     int force_ldss = -1;               // TM_HOP_LDS: 1 / 0 forces the LDS-staged variant where it exists
-    int force_nr = 0;                  // TM_HOP_NR: 1, 2 or 4 rhs per thread where instantiated (0: default)
+    int force_nr = 0;                  // TM_HOP_NR: rhs per thread where instantiated, per block of the split kernel (0: default)
+    int force_split = -1;              // TM_HOP_SPLIT: 1 / 0 forces the direction-split kernel on / off
     int force_nt = -1;                 // TM_HOP_NT: non-temporal stream mask of the hop launches (see HopCfg)
     int cg_fuse = 1;                   // TM_CG_FUSE=0: CG residual update as a separate BLAS pass
     int verbose = 0;                   // TM_VERBOSE=1: solver progress on stderr
+    bool solving = false;              // inside a CG run: the next operator reads the same links
     const int *gate = nullptr;         // set while enqueuing gated (device-decided) launches
     int xcd_remap = 1;
     unsigned lds_per_cu = 0;           // from the runtime at context creation
@@ -245,6 +247,8 @@ int red_slot(tm_ctx *ctx, int i, size_t npartials, RedSlot *out)
 
 // ------------------------------------------------------------------ hop launch
 
+constexpr int kAgainLinks = 1, kAgainOut = 2;
+
 struct HopCall {
     const tm_gauge *g;
     int prec;
@@ -261,23 +265,9 @@ struct HopCall {
     CGScalars *cg;
     double *red_out;
     int upd = 0;             // CG residual update: out -= alpha (epilogue result), alpha from cg
+    int again = 0;           // the caller's next launch reads these links again (kAgainLinks) / this
+                             // output (kAgainOut): keep them cached if they fit
 };
-
-#ifndef TM_FP64_NR
-#define TM_FP64_NR 2
-#endif
-constexpr int kFp64Nr = TM_FP64_NR;
-
-// rhs per thread (one flavour, 12-real links): 4 for the reduced precisions,
-// 2 for FP64 (an FP64 site vector for 4 rhs alone needs 192 VGPRs); force
-// (1, 2 or 4) overrides where that variant exists.
-int choose_nr(int prec, int nf, int nrhs, int recon, int force)
-{
-    if (nf != 1 || recon != 12) return 1;
-    if (force == 1 || force == 2 || (force == 4 && prec != TM_FP64)) return nrhs % force ? 1 : force;
-    const int want = (prec == TM_FP64) ? kFp64Nr : 4;
-    return nrhs % want ? 1 : want;
-}
 
 // Launch configurations instantiated for a hop variant (see TM_HOP_DEFINE):
 // block size, and whether links are loaded non-temporally (bypassing the
@@ -291,8 +281,9 @@ struct HopCfg {
     bool lnt;
     int wcap;
     int zc = 0;     // z-planes per brick of the site order (0: lexicographic)
+    bool split = false;  // direction-split kernel (bs = kSplitThreads, no wave cap, no staging)
     bool ldss = false;   // x / y neighbours staged in LDS (FP32, one flavour, one rhs)
-    int nr = 1;     // right-hand sides per thread
+    int nr = 1;     // right-hand sides per thread (direction-split: per block)
     // streams accessed non-temporally (HopBatch::nt_streams): 1 output
     // stores, 2 xpay operand loads, 4 time-neighbour loads.  Streaming the
     // single-use fields past L2 leaves it to the neighbour spinors that are
@@ -301,19 +292,25 @@ struct HopCfg {
     int nt = 0;
 };
 // cache code of a tuned configuration: block size in bits 0-9, the
-// non-temporal stream mask in bits 10-12
+// non-temporal stream mask in bits 10-12, the direction-split kernel bit 13
+// (its rhs per block in the wave-cap field)
 int cfg_code(const HopCfg &c)
 {
-    const int l2nr = c.nr == 4 ? 2 : c.nr == 2 ? 1 : 0;
-    return c.bs | ((c.nt & 7) << 10) | (c.lnt ? 1 << 16 : 0) | (c.ldss ? 1 << 17 : 0) | (l2nr << 18) |
-           (c.wcap << 20) | (c.zc << 24);
+    const int l2nr = c.split ? 0 : c.nr == 4 ? 2 : c.nr == 2 ? 1 : 0;
+    return c.bs | ((c.nt & 7) << 10) | (c.split ? 1 << 13 : 0) | (c.lnt ? 1 << 16 : 0) | (c.ldss ? 1 << 17 : 0) |
+           (l2nr << 18) | ((c.split ? c.nr : c.wcap) << 20) | (c.zc << 24);
 }
 HopCfg cfg_decode(int code)
 {
-    HopCfg c{code & 0x3ff, ((code >> 16) & 1) != 0, (code >> 20) & 0xf, (code >> 24) & 0x7f,
-             ((code >> 17) & 1) != 0};
+    HopCfg c{code & 0x3ff, ((code >> 16) & 1) != 0, (code >> 20) & 0xf, (code >> 24) & 0x7f};
+    c.ldss = ((code >> 17) & 1) != 0;
     c.nr = 1 << ((code >> 18) & 3);
     c.nt = (code >> 10) & 7;
+    c.split = ((code >> 13) & 1) != 0;
+    if (c.split) {
+        c.nr = std::max(1, c.wcap);
+        c.wcap = 0;
+    }
     return c;
 }
 // bricks of at most `target` z-planes: the largest divisor of Lz below Lz
@@ -367,6 +364,10 @@ std::vector<HopCfg> cfg_candidates(int prec, int nf, int nr, int twl, int recon,
                            : clv ? std::vector<int>{64, 256}
                            : (nr == 1) ? std::vector<int>{64, 128, 256} : std::vector<int>{128, 256};
     std::vector<HopCfg> out;
+    if (nr == 1 && !clv) {
+        out.push_back({kSplitThreads, true, 0, 0, true});
+        out.push_back({kSplitThreads, false, 0, 0, true});
+    }
     for (int b : bss)
         for (int w : {0, 4, 3, 2}) {
             out.push_back({b, true, w});
@@ -376,18 +377,116 @@ std::vector<HopCfg> cfg_candidates(int prec, int nf, int nr, int twl, int recon,
     if (prec == TM_FP32 && nf == 1 && nr == 1 && recon == 12 && !clv)
         for (int b : {64, 256})
             for (int w : {0, 3, 2}) {
-                out.push_back({b, true, w, 0, true});
-                out.push_back({b, false, w, 0, true});
+                out.push_back({b, true, w, 0, false, true});
+                out.push_back({b, false, w, 0, false, true});
             }
     return out;
 }
 
-// Default when not tuned: 256 threads; ordinary link loads when the launch's
-// links and three spinor fields fit well inside the last-level cache.
-HopCfg default_cfg(int twl, size_t working_set)
+// Right-hand sides per block of the direction-split kernel (FP32 / FP64, one
+// flavour, 12-real links): the links are loaded once per block, so more is
+// better until the blocks no longer fill the chip evenly.  `slots` blocks run
+// at once (three per compute unit in FP32, four of the single-rhs kernel with
+// its one LDS buffer, two in FP64); a block's
+// time is about its rhs and 1.5 more for the links and the start, and the
+// launch takes the rounds its blocks need.  16^3 x 32 FP32, 12 rhs, R^-1 D:
+// 1 / 2 / 3 / 4 / 6 / 12 per block 65 / 57 / 54 / 51 / 49 / 53 us (four per
+// thread of the one-thread kernel: 90).
+int split_group(const HopCall *calls, int n, int prec)
 {
+    int most = 1, best = 1;
+    for (int i = 0; i < n; i++) most = std::max(most, calls[i].nrhs);
+    double t_best = 1e30;
+    for (int q = 1; q <= std::min(most, 12); q++) {
+        const long slots = prec == TM_FP64 ? 512 : q == 1 ? 1024 : 768;
+        long blocks = 0;
+        for (int i = 0; i < n; i++)
+            blocks += (long)((calls[i].g->vh + kSplitSites - 1) / kSplitSites) * ((calls[i].nrhs + q - 1) / q);
+        const double t = (double)((blocks + slots - 1) / slots) * (q + 1.5);
+        if (t < t_best) {
+            t_best = t;
+            best = q;
+        }
+    }
+    return best;
+}
+
+// Launch shape when not tuned (may_split: 0 one-thread kernel, 1 by the rule
+// below, 2 direction-split wherever it exists, with
+// group rhs per block if not 0).  Times: us of R^-1 D / R x + k D, rotating
+// over three sets of fields; "tuned" is the tuner's best one-thread shape.
+HopCfg default_cfg(const HopCall *calls, int n, int prec, int nf, int twl, int recon, bool clv, size_t link_bytes,
+                   size_t working_set, int may_split, int group)
+{
+    long work = 0;
+    int nrhs = 1;
+    for (int i = 0; i < n; i++) {
+        work += (long)calls[i].g->vh * calls[i].nrhs;
+        nrhs = std::max(nrhs, calls[i].nrhs);
+    }
+    const bool half = prec == TM_FP16 || prec == TM_BF16;
+    // What the last-level cache (256 MB) keeps from launch to launch.  M^
+    // (asymmetric, us), links ordinary / non-temporal in its two launches:
+    // 24^3 x 48 FP32 (127 MB of links) ordinary then non-temporal 71, both
+    // non-temporal 75, both ordinary 77; the same operator repeated on one
+    // gauge field, as a solver does, 70 / 75 / 65.  FP64 at 24^3 x 48 (254 MB)
+    // is fastest non-temporal throughout.  With several rhs the links of a
+    // block are those of the next.
+    const int again = calls[0].again;
+    HopCfg c{256, nrhs == 1 && link_bytes > ((again & kAgainLinks) ? (size_t)160 << 20 : (size_t)100 << 20), 0};
+    // Single-use fields past L2: the xpay operand when the working set leaves
+    // the last-level cache (24^3 x 48 FP32 doublet 113 against 120, 16^3 x 32
+    // with 12 rhs 103 against 112; within it 71 against 74 the other way), the
+    // output unless the next launch reads it.
+    const bool large = working_set > (size_t)130 << 20;
+    if (clv) {
+        // clover epilogues: latency of the blocks' loads, whatever the rest
+        if (work <= 20000) c.bs = 64;
+        c.nt = (again & kAgainOut) ? 0 : kNtOut;
+        return c;
+    }
+    c.nt = (working_set > (size_t)230 << 20 ? kNtX : 0) | kNtOut;
+    // Direction-split kernel: always for one FP32 flavour (128 sites 5.1
+    // against 5.5 us of launch-bound time, 24^3 x 48 36 / 39 against 39 / 43
+    // tuned, 32^3 x 64 106 / 124 against 110 / 125).  Elsewhere up to the size
+    // where the one-thread kernel's fewer LDS passes and waves win: FP32
+    // doublet (24^3 x 48 56 / 68 against 61 / 69 tuned, 32^3 x 64 179 / 211
+    // against 179 / 205), FP64 (20^3 x 40 38 / 41 against 39 / 43, 24^3 x 48
+    // 79 / 89 against 76 / 86; doublet 24^3 x 48 139 / 159 against 144 / 163,
+    // 32^3 x 64 436 / 498 against 390 / 452), half precision, whose products
+    // cross LDS in FP32 (doublet 16^3 x 32 11.4 / 12.7 against 11.8 / 13.3,
+    // 20^3 x 40 24 / 28 against 20 / 22; one flavour 16^3 x 32 6.9 / 7.3
+    // against 8.0 / 8.7, with two rhs 11 / 11 against 10 / 10).
+    const bool shared = nrhs > 1 && nf == 1 && recon == 12 && !twl && !half;   // several rhs per block
+    const bool fits = half ? work <= (nf == 2 ? 65536 : 100000)
+                     : prec == TM_FP32 ? nf == 1 || work * nf <= 1L << 20 : shared || work <= 250000L * nf;
+    if (may_split + (int)fits >= 2) {
+        c.bs = kSplitThreads;
+        c.split = true;
+        if (shared) c.nr = group ? group : split_group(calls, n, prec);
+        if ((again & kAgainOut) && (large || nf == 1)) c.nt &= ~kNtOut;   // 20^3 x 40 FP64 74 against 76
+        return c;
+    }
     if (twl) return {256, true, 0};
-    return {256, working_set > (size_t)200 << 20, 0};
+    // One thread per site: half precision in small blocks without a cap of the
+    // resident waves (32^3 x 64 doublet FP16 104 / 118, capped at three 112 /
+    // 127); FP64 and the FP32 doublet keep more neighbours in L2 with two
+    // waves per SIMD and bricks of eight z-planes (FP64 doublet 390 / 452
+    // against 422 / 505 without, FP32 doublet 179 / 206 against 191 / 229).
+    // 18-real links come in blocks of 256 only.
+    if (recon == 18) {
+        if (!half) {
+            c.wcap = 2;
+            c.zc = 8;
+        }
+    } else if (half) {
+        c.bs = 64;
+    } else if (work > 131072) {
+        c.bs = (prec == TM_FP64 && nf == 2) ? 256 : 64;
+        c.wcap = 2;
+        c.zc = 8;
+    }
+    return c;
 }
 
 std::string tune_key(int prec, int nf, int nr, int dagger, int twl, int epi, int recon, long vh_total,
@@ -426,6 +525,15 @@ void load_tune(tm_ctx *ctx)
 hipError_t dispatch_hop(const HopBatch &B, int prec, int nf, int nr, int dagger, int twl, int recon,
                         const HopCfg &c, bool clv, unsigned lds, hipStream_t st, hipFuncAttributes *attr = nullptr)
 {
+    if (c.split) {
+        switch (prec) {
+        case TM_FP64: return launch_hop_split<TM_FP64>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, st);
+        case TM_FP32: return launch_hop_split<TM_FP32>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, st);
+        case TM_FP16: return launch_hop_split<TM_FP16>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, st);
+        case TM_BF16: return launch_hop_split<TM_BF16>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, st);
+        }
+        return hipErrorInvalidValue;
+    }
     switch (prec) {
     case TM_FP64: return launch_hop_prec<TM_FP64>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, st, attr);
     case TM_FP32: return launch_hop_prec<TM_FP32>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, st, attr);
@@ -450,7 +558,7 @@ int hop_lds_plan(tm_ctx *ctx, const HopBatch &B, int prec, int nf, int nr, int d
         staging = hop_staging_bytes(c.bs, row);
     }
     *lds = 0;
-    if (c.wcap <= 0 && staging == 0) return TM_OK;
+    if (c.split || (c.wcap <= 0 && staging == 0)) return TM_OK;
     char key[96];
     snprintf(key, sizeof(key), "%d_%d_%d_%d_%d_%d_%d_%d_%d_%d", prec, nf, nr, dagger, twl, recon, c.bs, (int)c.lnt,
              (int)clv, (int)c.ldss);
@@ -480,16 +588,16 @@ int hop_lds_plan(tm_ctx *ctx, const HopBatch &B, int prec, int nf, int nr, int d
 
 // One launch of the fused hop over up to kMaxProblems problems (same
 // precision, flavour count, recon, dagger, epilogue and rhs grouping).
-int build_hop_batch(tm_ctx *ctx, const HopCall *calls, int n, int nr, int bs, HopBatch *B, int zc = 0,
-                    int nt = 0)
+int build_hop_batch(tm_ctx *ctx, const HopCall *calls, int n, const HopCfg &cfg, HopBatch *B)
 {
+    const int nr = cfg.nr, zc = cfg.zc;
     const int prec = calls[0].prec, nf = calls[0].g->nf;
     memset(B, 0, sizeof(*B));
     B->nprob = n;
     B->gate = ctx->gate;
     B->epi = calls[0].epi;
     B->xcd_remap = ctx->xcd_remap;
-    B->nt_streams = nt;
+    B->nt_streams = cfg.nt;
     int blocks = 0;
     for (int i = 0; i < n; i++) {
         const HopCall &c = calls[i];
@@ -500,9 +608,14 @@ int build_hop_batch(tm_ctx *ctx, const HopCall *calls, int n, int nr, int bs, Ho
         hp.vh = (int)g->vh;
         hp.nrhs = c.nrhs;
         hp.blk_start = blocks;
-        const int spb = (nf == 2 && kNdSplit) ? bs / 2 : bs;      // sites per block
+        // sites per block
+        const int spb = cfg.split ? kSplitSites : (nf == 2 && kNdSplit) ? cfg.bs / 2 : cfg.bs;
         hp.nsb = (int)((g->vh + spb - 1) / spb);
-        hp.ngrp = c.nrhs / nr;
+        hp.ngrp = (c.nrhs + nr - 1) / nr;
+        hp.nrg = nr;
+        hp.dx.set((uint32_t)g->p.dims[0] / 2);
+        hp.dy.set((uint32_t)g->p.dims[1]);
+        hp.dz.set((uint32_t)g->p.dims[2]);
         hp.out_parity = c.out_parity;
         hp.zc = zc ? zc_for(zc, g->p.dims[2]) : 0;
         // slabs of about an eighth of the time extent (one XCD's share)
@@ -589,47 +702,64 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
         }
         return launch_hops(ctx, pre, n);
     }
-    // rhs per thread: the instantiated groupings that divide every problem's
-    // rhs count are tuning candidates; the heuristic choice is the default
-    std::vector<int> nrs;
-    for (int q : {1, 2, 4}) {
-        bool ok = q == 1 || (nf == 1 && recon == 12 && !clv && !(q == 4 && prec == TM_FP64));
-        for (int i = 0; i < n && ok; i++) ok = calls[i].nrhs % q == 0;
-        if (ok) nrs.push_back(q);
-    }
+    // rhs per thread of the one-thread kernel: one, or as a tuning candidate
+    // two in half precision where they divide every problem's count
+    // (24^3 x 48 FP16, four rhs: 68 / 75 against 70 / 78 us; in FP32 / FP64 the
+    // direction-split kernel shares the links better: 97 against 111)
+    const bool half = prec == TM_FP16 || prec == TM_BF16;
+    std::vector<int> nrs{1};
+    bool two = half && nf == 1 && recon == 12 && !clv && !twl;
+    for (int i = 0; i < n && two; i++) two = calls[i].nrhs % 2 == 0;
+    if (two) nrs.push_back(2);
     if (ctx->force_nr && std::find(nrs.begin(), nrs.end(), ctx->force_nr) != nrs.end()) nrs = {ctx->force_nr};
-    int nr_def = 1 << 30;
-    for (int i = 0; i < n; i++) nr_def = std::min(nr_def, choose_nr(prec, nf, calls[i].nrhs, recon, ctx->force_nr));
-    if (clv || std::find(nrs.begin(), nrs.end(), nr_def) == nrs.end()) nr_def = 1;
     // LDS staging only where the block's rows fit in half a compute unit's LDS
     int xrow = 0;
     for (int i = 0; i < n; i++) xrow = std::max(xrow, calls[i].g->p.dims[0] / 2);
     const unsigned lds_cu = ctx->lds_per_cu ? ctx->lds_per_cu : kLdsPerCUDefault;
     auto staging_fits = [&](int bs) { return hop_staging_bytes(bs, xrow) <= lds_cu / 2; };
+    // any other forced choice asks for the one-thread kernel
+    const bool forced = ctx->force_bs || ctx->force_lnt >= 0 || ctx->force_zc >= 0 || ctx->force_wcap >= 0 ||
+                        ctx->force_ldss >= 0 || ctx->force_nr || ctx->force_nt >= 0;
+    const int may_split = ctx->force_split >= 0 ? 2 * ctx->force_split : forced ? 0 : 1;
     std::vector<HopCfg> cand;
     for (int q : nrs)
         for (HopCfg c : cfg_candidates(prec, nf, q, twl, recon, clv)) {
             c.nr = q;
             if (c.ldss && !staging_fits(c.bs)) continue;
+            // the direction-split kernel where it could win (see default_cfg)
+            if (c.split && !may_split) continue;
+            if (ctx->force_split > 0 && !c.split) continue;
             cand.push_back(c);
         }
     long vh_total = 0;
-    size_t wset = 0;
+    size_t wset = 0, lset = 0;
     for (int i = 0; i < n; i++) {
         const tm_gauge *g = calls[i].g;
         vh_total += (long)g->vh * calls[i].nrhs;
-        wset += 2 * gauge_parity_bytes(prec, recon, g->vh) + 3 * spinor_field_bytes(prec, g->vh, nf, calls[i].nrhs);
+        lset += 2 * gauge_parity_bytes(prec, recon, g->vh);
+        wset += 3 * spinor_field_bytes(prec, g->vh, nf, calls[i].nrhs);
     }
-    HopCfg cfg = default_cfg(twl, wset);
-    cfg.nr = nr_def;
+    wset += lset;
+    HopCfg cfg = default_cfg(calls, n, prec, nf, twl, recon, clv, lset, wset,
+                             may_split, std::min(ctx->force_nr, 12));
+    if (ctx->tuning && cfg.split && cfg.nr > 1)
+        for (int q : {2, 4, cfg.nr})
+            if (q <= cfg.nr) {
+                cand.push_back(cfg);
+                cand.back().nr = q;
+            }
+    if (!cfg.split && std::find(nrs.begin(), nrs.end(), ctx->force_nr) != nrs.end()) {
+        cfg.nr = ctx->force_nr;
+        if (cfg.nr > 1) cfg.bs = std::max(cfg.bs, 128);   // two rhs per thread: blocks of 128 and 256
+    }
     const std::string key = tune_key(prec, nf, nrs.back(), dagger, twl, calls[0].epi, recon, vh_total, clv);
     auto it = ctx->tuned.find(key);
-    if (ctx->force_bs || ctx->force_lnt >= 0) {
+    if (!cfg.split && (ctx->force_bs || ctx->force_lnt >= 0)) {
         HopCfg want{ctx->force_bs ? ctx->force_bs : cfg.bs, ctx->force_lnt >= 0 ? ctx->force_lnt != 0 : cfg.lnt,
                     0};
-        want.nr = nr_def;
+        want.nr = cfg.nr;
         for (const HopCfg &c : cand)
-            if (c.bs == want.bs && c.lnt == want.lnt && c.wcap == 0 && c.nr == want.nr) cfg = want;
+            if (!c.split && c.bs == want.bs && c.lnt == want.lnt && c.wcap == 0 && c.nr == want.nr) cfg = want;
     } else if (it != ctx->tuned.end()) {
         cfg = cfg_decode(it->second);
     } else if (ctx->tuning && cand.size() > 1 && !ctx->gate && !ctx->no_alloc) {
@@ -661,7 +791,7 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
             auto trial = [&](const HopCfg &c, int reps, float *ms_per) -> int {
                 HopBatch B;
                 unsigned lds = 0;
-                TM_TRY(build_hop_batch(ctx, tc, n, c.nr, c.bs, &B, c.zc, c.nt));
+                TM_TRY(build_hop_batch(ctx, tc, n, c, &B));
                 TM_TRY(hop_lds_plan(ctx, B, prec, nf, c.nr, dagger, twl, recon, c, clv, &lds));
                 TM_HIP(ctx, dispatch_hop(B, prec, nf, c.nr, dagger, twl, recon, c, clv, lds, ctx->stream));
                 TM_HIP(ctx, hipEventRecord(e0, ctx->stream));
@@ -681,7 +811,7 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
             for (const HopCfg &c : cand) {
                 HopBatch B;
                 unsigned lds = 0;
-                TM_TRY(build_hop_batch(ctx, tc, n, c.nr, c.bs, &B, c.zc, c.nt));
+                TM_TRY(build_hop_batch(ctx, tc, n, c, &B));
                 if (hop_lds_plan(ctx, B, prec, nf, c.nr, dagger, twl, recon, c, clv, &lds, true) != TM_OK) continue;
                 float ms;
                 TM_TRY(trial(c, 4, &ms));
@@ -740,16 +870,17 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
         }
     }
     if (ctx->force_zc >= 0) cfg.zc = ctx->force_zc;
-    if (ctx->force_ldss >= 0 && (ctx->force_ldss == 0 || (prec == TM_FP32 && nf == 1 && cfg.nr == 1 &&
+    if (!cfg.split && ctx->force_ldss >= 0 && (ctx->force_ldss == 0 || (prec == TM_FP32 && nf == 1 && cfg.nr == 1 &&
                                                             recon == 12 && !clv && !twl &&
                                                             staging_fits(cfg.bs))))
         cfg.ldss = ctx->force_ldss != 0;
     if (cfg.ldss) cfg.zc = 0;
-    if (ctx->force_wcap >= 0) cfg.wcap = ctx->force_wcap;
+    if (cfg.split && ctx->force_lnt >= 0) cfg.lnt = ctx->force_lnt != 0;
+    if (!cfg.split && ctx->force_wcap >= 0) cfg.wcap = ctx->force_wcap;
     if (ctx->force_nt >= 0) cfg.nt = ctx->force_nt;
     HopBatch B;
     unsigned lds = 0;
-    TM_TRY(build_hop_batch(ctx, calls, n, cfg.nr, cfg.bs, &B, cfg.zc, cfg.nt));
+    TM_TRY(build_hop_batch(ctx, calls, n, cfg, &B));
     TM_TRY(hop_lds_plan(ctx, B, prec, nf, cfg.nr, dagger, twl, recon, cfg, clv, &lds));
     TM_HIP(ctx, dispatch_hop(B, prec, nf, cfg.nr, dagger, twl, recon, cfg, clv, lds, ctx->stream));
     TM_TRY(finish_reductions(ctx, B.p, n));
@@ -882,6 +1013,10 @@ int mat_pc_batch(tm_ctx *ctx, const tm_gauge *const *g, void *const *out, const 
             }
         }
     }
+    for (int i = 0; i < n; i++) {
+        k1[i].again = kAgainLinks | kAgainOut;
+        k2[i].again = ctx->solving ? kAgainLinks : 0;
+    }
     TM_TRY(launch_hops(ctx, k1, n));
     TM_TRY(launch_hops(ctx, k2, n));
     return TM_OK;
@@ -961,6 +1096,8 @@ int tm_ctx_create(tm_ctx **ctx, void *hip_stream)
     if (e) c->force_nr = atoi(e);
     e = getenv("TM_HOP_NT");
     if (e) c->force_nt = atoi(e) & 7;
+    e = getenv("TM_HOP_SPLIT");
+    if (e) c->force_split = atoi(e) ? 1 : 0;
     e = getenv("TM_CG_FUSE");
     if (e) c->cg_fuse = atoi(e) ? 1 : 0;
     e = getenv("TM_VERBOSE");
@@ -1475,6 +1612,11 @@ struct GraphCache {
 int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_cg_result *res)
 {
     const auto t0 = std::chrono::steady_clock::now();
+    struct Solving {
+        tm_ctx *c;
+        ~Solving() { c->solving = false; }
+    } solving{ctx};
+    ctx->solving = true;
     const int n = (int)pr.size();
     const int pc = par->pc;
     const int inner = par->inner;

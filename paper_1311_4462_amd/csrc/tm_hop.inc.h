@@ -3,7 +3,7 @@
 // for the non-degenerate doublet with each link loaded once for both flavours).
 //
 // One thread computes one output site for NR right-hand sides and NF
-// flavours.  For every direction it loads the link (rebuilding row 2 from
+// flavours (NR = 2 in half precision only).  For every direction it loads the link (rebuilding row 2 from
 // rows 0, 1 when 12 reals are stored), loads the neighbour (only the spin
 // pair the time projector keeps, in the basis of Sec. 2), spin-projects to a
 // half spinor, multiplies by U or U^+, and rebuilds the lower spin pair.
@@ -882,14 +882,10 @@ __global__ void __launch_bounds__(BS, (hop_waves<P, NF, NR, CLV, TWL>())) hop_ke
         TM_HOP_CASES(P, 2, 1, 8, 256)                                                          \
         TM_HOP_CASES(P, 2, 1, 8, 128)                                                          \
         TM_HOP_CASES(P, 2, 1, 8, 64)                                                           \
-        if constexpr (P != TM_FP64) {                                                          \
-            TM_HOP_CASES(P, 1, 4, 12, 256)                                                     \
-            TM_HOP_CASES(P, 1, 4, 12, 128)                                                     \
-            TM_HOP_CASES_TWL(P, 1, 4, 12)                                                      \
+        if constexpr (P == TM_FP16 || P == TM_BF16) {                                          \
+            TM_HOP_CASES(P, 1, 2, 12, 256)                                                     \
+            TM_HOP_CASES(P, 1, 2, 12, 128)                                                     \
         }                                                                                      \
-        TM_HOP_CASES(P, 1, 2, 12, 256)                                                         \
-        TM_HOP_CASES(P, 1, 2, 12, 128)                                                         \
-        TM_HOP_CASES_TWL(P, 1, 2, 12)                                                          \
         TM_HOP_CASES_TWL(P, 1, 1, 12)                                                          \
         TM_HOP_CASES_TWL(P, 1, 1, 18)                                                          \
         TM_HOP_CASES_TWL(P, 2, 1, 12)                                                          \

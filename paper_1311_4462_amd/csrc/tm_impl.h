@@ -20,6 +20,9 @@ constexpr int kMaxProblems = 8;   // problems per batched launch
 #endif
 constexpr bool kNdSplit = TM_ND_SPLIT != 0;
 constexpr int kBlock = 256;       // default threads per block
+// direction-split hop kernel: sites of a block, and its threads (one wave per hop)
+constexpr int kSplitSites = 64;
+constexpr int kSplitThreads = 8 * kSplitSites;
 // Device scratch of the allocation-free operator call: 256 MiB per GPU
 // (the odd temporary of the 32^3 x 64 FP32 doublet operator is 192 MiB).
 constexpr size_t kNoAllocScratchBytes = (size_t)256 << 20;
@@ -192,6 +195,11 @@ __device__ __forceinline__ void st_nt(uint4 *p, uint4 v)
 {
     __builtin_nontemporal_store((nt_u4){v.x, v.y, v.z, v.w}, (nt_u4 *)p);
 }
+__device__ __forceinline__ void st_nt(float2 *p, float2 v)
+{
+    __builtin_nontemporal_store((nt_f2){v.x, v.y}, (nt_f2 *)p);
+}
+__device__ __forceinline__ void st_nt(uint32_t *p, uint32_t v) { __builtin_nontemporal_store(v, p); }
 template <bool NT, typename T>
 __device__ __forceinline__ T lds_(const T *p)
 {
@@ -891,13 +899,31 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
 
 // ------------------------------------------------------------------ hop descriptors
 
+// Division of n < 2^31 by a constant: floor(n / d) = (mulhi(n, m) + n) >> s
+// with s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1.
+struct FastDiv {
+    uint32_t m, s;
+    void set(uint32_t d)
+    {
+        s = 0;
+        while ((1u << s) < d) s++;
+        m = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << s) - d)) / d + 1);
+    }
+    __host__ __device__ uint32_t div(uint32_t n) const
+    {
+        return ((uint32_t)(((uint64_t)n * m) >> 32) + n) >> s;
+    }
+};
+
 struct HopProblem {
     int X[4];            // Lx, Ly, Lz, Lt
+    FastDiv dx, dy, dz;  // by Lx / 2, Ly, Lz
     int vh;              // sites per parity
     int nrhs;
     int blk_start;       // first logical block of this problem
     int nsb;             // site blocks
     int ngrp;            // rhs groups
+    int nrg;             // rhs per group
     int out_parity;
     int zc;              // z-planes per brick of the processing order (0: lexicographic)
     int ts;              // time slices per slab of the processing order (zc > 0)

@@ -65,6 +65,8 @@ struct tm_ctx {
     int verbose = 0;                   // TM_VERBOSE=1: solver progress on stderr
     bool solving = false;              // inside a CG run: the next operator reads the same links
     const int *gate = nullptr;         // set while enqueuing gated (device-decided) launches
+    int *gate_copy = nullptr;          // the next hop launch copies its gate here, and later ones use the copy
+    CGPost post{};                     // flags of the CG run whose iterations are being enqueued
     int xcd_remap = 1;
     unsigned lds_per_cu = 0;           // from the runtime at context creation
     unsigned lds_per_block = 0;
@@ -671,6 +673,7 @@ int finish_reductions(tm_ctx *ctx, const Prob *p, int n)
     if (!any) return TM_OK;
     F.nprob = n;
     F.gate = ctx->gate;
+    if (p[0].red.op == FIN_BETA || p[0].red.op == FIN_RELIABLE) F.post = ctx->post;
     TM_HIP(ctx, launch_finish(F, ctx->stream));
     return TM_OK;
 }
@@ -882,8 +885,19 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
     unsigned lds = 0;
     TM_TRY(build_hop_batch(ctx, calls, n, cfg, &B));
     TM_TRY(hop_lds_plan(ctx, B, prec, nf, cfg.nr, dagger, twl, recon, cfg, clv, &lds));
+    // A small launch of the direction-split kernel finishes its reductions
+    // itself, while the blocks' counts on one address take less than the
+    // finish launch: FP64 CG at 8^3 x 16 (64 blocks) 2100 -> 1990 us, at
+    // 12^3 x 24 (324 blocks) 2760 -> 2880.
+    B.post = ctx->post;
+    B.finish_here = cfg.split && calls[0].fin != FIN_NONE && ctx->post.flags && B.total_blocks <= 64;
+    B.gate_copy = ctx->gate_copy;
     TM_HIP(ctx, dispatch_hop(B, prec, nf, cfg.nr, dagger, twl, recon, cfg, clv, lds, ctx->stream));
-    TM_TRY(finish_reductions(ctx, B.p, n));
+    if (ctx->gate_copy) {
+        ctx->gate = ctx->gate_copy;
+        ctx->gate_copy = nullptr;
+    }
+    if (!B.finish_here) TM_TRY(finish_reductions(ctx, B.p, n));
     return TM_OK;
 }
 
@@ -1797,39 +1811,22 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         return true_residual(ctx, pr, pc, lp, rv, nullptr, FIN_RELIABLE);
     };
 
-    // Device-side control of every iteration (eager or captured):
-    //   flags[0]  reliable-update gate (mixed: decided on the device each
-    //             iteration, its launches gated by it)
-    //   flags[1]  number of reliable updates taken
-    //   flags[2]  run flag: some rhs still iterates; every launch of an
-    //             iteration is gated by it, so iterations enqueued after
-    //             convergence do nothing
-    //   flags[3]  iterations that ran
-    int *flags = nullptr;
+    // Device-side control of every iteration (eager or captured), see CGFlags
+    CGFlags *flags = nullptr;
     {
         int rc = TM_OK;
-        flags = (int *)workspace(ctx, "cg_flags", 256, &rc);
+        flags = (CGFlags *)workspace(ctx, "cg_flags", 256, &rc);
         if (!flags) return rc;
         TM_HIP(ctx, hipMemsetAsync(flags, 0, 256, ctx->stream));
     }
-    int *const upd_gate = flags, *const upd_count = flags + 1, *const run_flag = flags + 2,
-              *const iter_count = flags + 3;
-    RunArgs RA;
-    memset(&RA, 0, sizeof(RA));
-    DecideArgs D;
-    memset(&D, 0, sizeof(D));
-    RA.nprob = D.nprob = n;
+    FinishBatch start;
+    memset(&start, 0, sizeof(start));
+    start.nprob = n;
     for (int i = 0; i < n; i++) {
-        RA.nrhs[i] = D.nrhs[i] = pr[i].nrhs;
-        RA.cg[i] = D.cg[i] = pr[i].cg;
+        start.r[i].cg = pr[i].cg;
+        start.r[i].nvec = pr[i].nrhs;
     }
-    RA.with_pending = mixed ? 1 : 0;
-    RA.maxiter = par->maxiter;
-    RA.run = run_flag;
-    RA.iters = iter_count;
-    D.delta2 = delta * delta;
-    D.gate = upd_gate;
-    D.count = upd_count;
+    start.post = CGPost{flags, delta * delta, mixed ? 1 : 0, par->maxiter};
 
     // Tune every hop the iterations launch before any launch is gated or
     // captured (the tuner times real launches and is skipped in both cases):
@@ -1851,21 +1848,21 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         }
     }
 
+    TM_HIP(ctx, launch_start(start, ctx->stream));
     auto iteration = [&]() -> int {
-        TM_HIP(ctx, launch_run(RA, ctx->stream));
-        ctx->gate = run_flag;
+        ctx->post = start.post;
+        ctx->gate = &flags->run;
+        ctx->gate_copy = &flags->ran;
         int rc = iteration_core();
         if (rc == TM_OK && mixed) {
-            rc = (launch_decide(D, ctx->stream) == hipSuccess) ? TM_OK
-                                                                : fail(ctx, TM_ERR_HIP, "decide launch");
-            if (rc == TM_OK) {
-                ctx->gate = upd_gate;
-                rc = reliable_update();
-                ctx->gate = run_flag;
-            }
+            ctx->gate = &flags->update;
+            rc = reliable_update();
+            ctx->gate = &flags->ran;
         }
         if (rc == TM_OK) rc = xpay();
         ctx->gate = nullptr;
+        ctx->gate_copy = nullptr;
+        ctx->post = CGPost{};
         return rc;
     };
 
@@ -1875,7 +1872,6 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         TM_HIP(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
         int rc = TM_OK;
         for (int k = 0; k < gk && rc == TM_OK; k++) rc = iteration();
-        ctx->gate = nullptr;
         hipGraph_t graph = nullptr;
         hipError_t e = hipStreamEndCapture(ctx->stream, &graph);
         if (rc != TM_OK) {
@@ -2014,6 +2010,7 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
                 done = all_inactive();
                 if (!done) {
                     // the chunk enqueued above was a no-op: iterate afresh
+                    TM_HIP(ctx, launch_start(start, ctx->stream));
                     launched = false;
                     in_flight = false;
                 }

@@ -663,6 +663,16 @@ __device__ __forceinline__ uint32_t site_of(const HopProblem &pb, uint32_t j)
     return ((so * (uint32_t)pb.ts + ti) * (uint32_t)pb.X[2] + ch * (uint32_t)pb.zc) * pl + r;
 }
 
+// Whether this launch is gated off; the first launch of a CG iteration leaves
+// the flag for the others of it.
+__device__ __forceinline__ bool gated_off(const HopBatch &B)
+{
+    if (!B.gate) return false;
+    const int g = *B.gate;
+    if (B.gate_copy && blockIdx.x == 0 && threadIdx.x == 0) *B.gate_copy = g;
+    return g == 0;
+}
+
 // CLV: twisted clover, the epilogue's twist is the per-site R(x) (clover
 // blocks of the output parity); twist-on-load is not combined with it.
 // LDSS: the input spinors of the block's sites and of one y-row either side
@@ -676,7 +686,7 @@ __global__ void __launch_bounds__(BS, (hop_waves<P, NF, NR, CLV, TWL>())) hop_ke
     static_assert(!CLV || (!TWL && NR == 1 && !nd_split<NF>() && (P == TM_FP64 || P == TM_FP32)),
                   "clover epilogues: FP64 / FP32, one rhs per thread, no twist-on-load");
     __shared__ double red_sh[BS / 64];
-    if (B.gate && *B.gate == 0) return;   // gated launch not needed this iteration
+    if (gated_off(B)) return;   // gated launch not needed this iteration
 
     const int lb = B.xcd_remap ? xcd_logical_block(blockIdx.x, B.total_blocks) : (int)blockIdx.x;
     int pi = 0;

@@ -839,38 +839,40 @@ struct Reduce {
     int nblk;
 };
 
+// Device-side control of the CG iterations (kept with the CG's workspace).
+// A launch of an iteration is gated by a flag here, so iterations enqueued past
+// convergence (the rest of a captured graph or of a host check period) do
+// nothing.
+struct CGFlags {
+    int update;      // the reliable update of this iteration runs (mixed)
+    int updates;     // reliable updates decided (for reporting)
+    int run;         // the next iteration runs
+    int iters;       // iterations that ran
+    int ran;         // this iteration runs: its first launch copies `run` here, the others
+                     // are gated by the copy, since `run` is set anew before the last of them
+    int done;        // blocks that have left their partials (launches that finish their own reduction)
+    int done_fin;    // the same for the blocks of the finish kernel
+};
+
+// What follows the reductions of an iteration's last hop (FIN_BETA) and of a
+// reliable update (FIN_RELIABLE), once every vector is finished.  After an
+// iteration: count it and decide its reliable update (mixed: any active rhs
+// whose rr fell below delta^2 maxrr, or any rhs whose iterated residual
+// converged and awaits verification).  After either: the next iteration runs
+// while some rhs is active (mixed: or awaits its verifying update) and fewer
+// than maxiter have run.
+struct CGPost {
+    CGFlags *flags;        // null: no flags to set
+    double delta2;
+    int mixed;
+    int maxiter;
+};
+
 struct FinishBatch {
     int nprob;
     const int *gate;       // nullable: skip the launch when *gate == 0
+    CGPost post;
     Reduce r[kMaxProblems];
-};
-
-// Device-side decision whether the next reliable update runs (mixed CG with
-// captured iterations): any active rhs whose rr fell below delta^2 maxrr, or
-// any rhs whose iterated residual converged and awaits verification.
-struct DecideArgs {
-    int nprob;
-    int nrhs[kMaxProblems];
-    CGScalars *cg[kMaxProblems];
-    double delta2;
-    int *gate;
-    int *count;            // number of updates decided (for reporting)
-};
-
-// Device-side run flag of a CG iteration: set when some rhs is still active
-// (or, with reliable updates, awaits its verifying update); every launch of
-// the iteration is gated by it, so iterations enqueued past convergence (the
-// rest of a captured graph, the rest of a host check period) do nothing.
-// iters counts the iterations that ran; once it reaches maxiter the flag
-// stays clear, so a check period never runs past the iteration limit.
-struct RunArgs {
-    int nprob;
-    int nrhs[kMaxProblems];
-    const CGScalars *cg[kMaxProblems];
-    int with_pending;
-    int maxiter;
-    int *run;
-    int *iters;
 };
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -895,6 +897,98 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
     }
     __syncthreads();
     return s;
+}
+
+// Apply the finishing operation of a reduction to vector v, whose sum is s
+// (one thread).
+__device__ __forceinline__ void finish_apply(const Reduce &rd, int v, double s)
+{
+    if (rd.op == FIN_STORE) {
+        rd.out[v] = s;
+    } else if (rd.op == FIN_ALPHA) {
+        CGScalars &c = rd.cg[v];
+        c.pap = s;
+        c.alpha = (c.active && s > 0.0) ? c.rr / s : 0.0;
+    } else if (rd.op == FIN_BETA) {
+        CGScalars &c = rd.cg[v];
+        if (c.active) {
+            c.beta = (c.rr > 0.0) ? s / c.rr : 0.0;
+            c.rr_old = c.rr;
+            c.rr = s;
+            c.maxrr = fmax(c.maxrr, s);
+            c.hist[c.niter % kHistory] = s;
+            c.niter++;
+            if (s <= c.stop2) {
+                c.active = 0;
+                c.pending = 1;
+            }
+        } else {
+            c.beta = 0.0;
+        }
+    } else if (rd.op == FIN_RELIABLE) {
+        // the residual was replaced by the true one (reliable update):
+        // continue the recurrence with beta = |r_true|^2 / |r_prev|^2
+        CGScalars &c = rd.cg[v];
+        // progress of the true residual from one replacement to the
+        // next, for rhs that were iterating (a converged rhs shares
+        // the replacements of the others without moving)
+        if (c.active || c.pending) {
+            if (c.rr_upd > 0.0 && s >= c.stall_f2 * c.rr_upd)
+                c.stall++;
+            else
+                c.stall = 0;
+            c.rr_upd = s;
+        }
+        c.beta = (c.rr_old > 0.0) ? s / c.rr_old : 0.0;
+        // the step alpha p of this iteration is in x already (taken
+        // before the replacement); a later pass of it adds nothing
+        c.alpha = 0.0;
+        c.rr = s;
+        c.maxrr = s;
+        c.active = (s > c.stop2) ? 1 : 0;
+        c.pending = 0;
+    } else if (rd.op == FIN_STORE_RR) {
+        // a fresh residual: restart the recurrence for this rhs
+        CGScalars &c = rd.cg[v];
+        c.rr = s;
+        c.rr_old = s;
+        c.maxrr = s;
+        c.beta = 0.0;
+        c.active = (s > c.stop2) ? 1 : 0;
+        c.pending = 0;
+        c.rr_upd = s;
+        c.stall = 0;
+    }
+}
+
+// The flags after a finished launch (see CGPost): all threads of one block,
+// after every vector's scalars are visible to them.  reduce(i): problem i's
+// reduction.
+template <typename F>
+__device__ __forceinline__ void cg_post(const CGPost &P, int nprob, const F &reduce)
+{
+    int live = 0, need = 0;
+    for (int i = 0; i < nprob; i++) {
+        const Reduce &rd = reduce(i);
+        for (int r = (int)threadIdx.x; r < rd.nvec; r += (int)blockDim.x) {
+            const CGScalars &c = rd.cg[r];
+            if (c.active || (P.mixed && c.pending)) live = 1;
+            if (c.pending || (c.active && c.rr < P.delta2 * c.maxrr)) need = 1;
+        }
+    }
+    live = __syncthreads_or(live);
+    need = __syncthreads_or(need);
+    if (threadIdx.x == 0) {
+        CGFlags &f = *P.flags;
+        if (reduce(0).op == FIN_BETA) {
+            f.iters += 1;
+            f.update = (P.mixed && need) ? 1 : 0;
+            f.updates += f.update;
+        } else {
+            f.update = 0;
+        }
+        f.run = (live && f.iters < P.maxiter) ? 1 : 0;
+    }
 }
 
 // ------------------------------------------------------------------ hop descriptors
@@ -943,6 +1037,9 @@ struct HopBatch {
     int nprob;
     int total_blocks;
     const int *gate;     // nullable: skip the launch when *gate == 0
+    int *gate_copy;      // nullable: receives *gate (the first launch of a CG iteration)
+    CGPost post;         // with finish_here
+    int finish_here;     // the last block finishes the reductions (direction-split kernel)
     int epi;             // tm_epilogue
     int xcd_remap;       // 1: give every XCD a contiguous range of blocks
     int nt_streams;      // kNtOut | kNtX | kNtTime: streams accessed non-temporally

@@ -267,6 +267,10 @@ struct HopCall {
     CGScalars *cg;
     double *red_out;
     int upd = 0;             // CG residual update: out -= alpha (epilogue result), alpha from cg
+    // true residual of a reliable update (FP64 hops): out = res_c - epilogue
+    // result, stored in precision res_prec (out then points to such a field)
+    const void *res_c = nullptr;
+    int res_prec = 0;
     int again = 0;           // the caller's next launch reads these links again (kAgainLinks) / this
                              // output (kAgainOut): keep them cached if they fit
 };
@@ -529,18 +533,18 @@ hipError_t dispatch_hop(const HopBatch &B, int prec, int nf, int nr, int dagger,
 {
     if (c.split) {
         switch (prec) {
-        case TM_FP64: return launch_hop_split<TM_FP64>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, st);
-        case TM_FP32: return launch_hop_split<TM_FP32>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, st);
-        case TM_FP16: return launch_hop_split<TM_FP16>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, st);
-        case TM_BF16: return launch_hop_split<TM_BF16>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, st);
+        case TM_FP64: return launch_hop_split<TM_FP64>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, B.res_prec >= 0, st);
+        case TM_FP32: return launch_hop_split<TM_FP32>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, B.res_prec >= 0, st);
+        case TM_FP16: return launch_hop_split<TM_FP16>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, B.res_prec >= 0, st);
+        case TM_BF16: return launch_hop_split<TM_BF16>(B, nf, dagger, twl, recon, c.lnt, c.nr > 1, B.res_prec >= 0, st);
         }
         return hipErrorInvalidValue;
     }
     switch (prec) {
-    case TM_FP64: return launch_hop_prec<TM_FP64>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, st, attr);
-    case TM_FP32: return launch_hop_prec<TM_FP32>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, st, attr);
-    case TM_FP16: return launch_hop_prec<TM_FP16>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, st, attr);
-    case TM_BF16: return launch_hop_prec<TM_BF16>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, st, attr);
+    case TM_FP64: return launch_hop_prec<TM_FP64>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, B.res_prec >= 0, st, attr);
+    case TM_FP32: return launch_hop_prec<TM_FP32>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, B.res_prec >= 0, st, attr);
+    case TM_FP16: return launch_hop_prec<TM_FP16>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, B.res_prec >= 0, st, attr);
+    case TM_BF16: return launch_hop_prec<TM_BF16>(B, nf, nr, dagger, twl, recon, c.bs, c.lnt, lds, clv, c.ldss, B.res_prec >= 0, st, attr);
     }
     return hipErrorInvalidValue;
 }
@@ -563,7 +567,7 @@ int hop_lds_plan(tm_ctx *ctx, const HopBatch &B, int prec, int nf, int nr, int d
     if (c.split || (c.wcap <= 0 && staging == 0)) return TM_OK;
     char key[96];
     snprintf(key, sizeof(key), "%d_%d_%d_%d_%d_%d_%d_%d_%d_%d", prec, nf, nr, dagger, twl, recon, c.bs, (int)c.lnt,
-             (int)clv, (int)c.ldss);
+             (int)clv, (int)c.ldss + 2 * (B.res_prec >= 0));
     unsigned static_lds;
     auto it = ctx->static_lds.find(key);
     if (it != ctx->static_lds.end()) {
@@ -595,6 +599,7 @@ int build_hop_batch(tm_ctx *ctx, const HopCall *calls, int n, const HopCfg &cfg,
     const int nr = cfg.nr, zc = cfg.zc;
     const int prec = calls[0].prec, nf = calls[0].g->nf;
     memset(B, 0, sizeof(*B));
+    B->res_prec = -1;
     B->nprob = n;
     B->gate = ctx->gate;
     B->epi = calls[0].epi;
@@ -639,6 +644,11 @@ int build_hop_batch(tm_ctx *ctx, const HopCall *calls, int n, const HopCfg &cfg,
         hp.x = c.x ? sptr(c.x, prec, g->vh, nf, c.nrhs) : SpinorPtr{nullptr, nullptr};
         if (c.upd && !c.cg) return fail(ctx, TM_ERR_ARG, "internal: residual update needs CG scalars");
         hp.upd = c.upd ? c.cg : nullptr;
+        if (c.res_c) {
+            hp.res = sptr(c.res_c, prec, g->vh, nf, c.nrhs);
+            hp.out = sptr(c.out, c.res_prec, g->vh, nf, c.nrhs);
+            B->res_prec = c.res_prec;
+        }
         hp.red.op = c.fin;
         if ((c.fin == FIN_ALPHA || c.fin == FIN_BETA || c.fin == FIN_STORE_RR || c.fin == FIN_RELIABLE) && !c.cg)
             return fail(ctx, TM_ERR_ARG, "internal: hop reduction needs CG scalars");
@@ -1006,7 +1016,7 @@ void *odd_tmp(tm_ctx *ctx, int slot, const tm_gauge *g, int prec, int nrhs, int 
 // Over n problems at once; `fin` reduces |out|^2 per rhs.
 int mat_pc_batch(tm_ctx *ctx, const tm_gauge *const *g, void *const *out, const void *const *in,
                  const int *nrhs, int n, int prec, int pc, int dagger, int fin, CGScalars *const *cg,
-                 bool upd = false)
+                 bool upd = false, const void *const *res_c = nullptr, int res_prec = 0)
 {
     HopCall k1[kMaxProblems], k2[kMaxProblems];
     for (int i = 0; i < n; i++) {
@@ -1028,6 +1038,10 @@ int mat_pc_batch(tm_ctx *ctx, const tm_gauge *const *g, void *const *out, const 
         }
     }
     for (int i = 0; i < n; i++) {
+        if (res_c) {
+            k2[i].res_c = res_c[i];
+            k2[i].res_prec = res_prec;
+        }
         k1[i].again = kAgainLinks | kAgainOut;
         k2[i].again = ctx->solving ? kAgainLinks : 0;
     }
@@ -1599,6 +1613,22 @@ int true_residual(tm_ctx *ctx, std::vector<CGProblem> &pr, int pc, int rp, void 
         ys[i] = pr[i].y;
         xs[i] = pr[i].x;
         mids[i] = pr[i].mid;
+    }
+    if (rp != TM_FP64 && !p && !pr[0].g->clover()) {
+        // the residual from the last hop: M^+ M x is not stored (a pass of two
+        // reads and a write, and its launch, less in every reliable update)
+        const tm_gauge *gs[kMaxProblems];
+        int nr[kMaxProblems];
+        CGScalars *cgs[kMaxProblems];
+        const void *cs[kMaxProblems];
+        for (int i = 0; i < n; i++) {
+            gs[i] = pr[i].g;
+            nr[i] = pr[i].nrhs;
+            cgs[i] = pr[i].cg;
+            cs[i] = pr[i].c;
+        }
+        TM_TRY(mat_pc_batch(ctx, gs, mids, xs, nr, n, TM_FP64, pc, 0, FIN_NONE, nullptr));
+        return mat_pc_batch(ctx, gs, r, (const void *const *)mids, nr, n, TM_FP64, pc, 1, fin, cgs, false, cs, rp);
     }
     TM_TRY(normal_op64(ctx, pr, pc, ys, mids, xs));
     BlasCall calls[kMaxProblems];

@@ -24,13 +24,13 @@ hipError_t noalloc_scratch(int device, void **ptr);
 // null, only fill attr with its function attributes (static LDS, registers).
 template <int P>
 hipError_t launch_hop_prec(const HopBatch &B, int nf, int nr, int dagger, int twl, int recon,
-                           int bs, bool lnt, unsigned lds, bool clv, bool ldss, hipStream_t st,
+                           int bs, bool lnt, unsigned lds, bool clv, bool ldss, bool res, hipStream_t st,
                            hipFuncAttributes *attr = nullptr);
 // Launch the direction-split variant (blocks of kSplitSites sites; mr: several
 // rhs per block, 12-real links).
 template <int P>
 hipError_t launch_hop_split(const HopBatch &B, int nf, int dagger, int twl, int recon, bool lnt, bool mr,
-                            hipStream_t st);
+                            bool res, hipStream_t st);
 // clover blocks of both parities (FP64 and / or FP32 destinations, nullable)
 hipError_t clover_build(void *const *d64, void *const *d32, const void *links, const int *X, uint32_t vh,
                         double kc, double shift, int *bad, hipStream_t st);

@@ -532,10 +532,12 @@ constexpr int fence_mode()
 // Epilogue of one output site for the thread's rhs: the twist / xpay of
 // tm_epilogue, the store, and the squared norm of the result for the
 // reduction (added to nrm).
-template <int P, int NF, int NR, bool CLV>
+// RES (FP64): the result becomes the true residual pb.res - A, rounded to
+// precision res_prec on its way out; the norm is that of the FP64 values.
+template <int P, int NF, int NR, bool CLV, bool RES>
 __device__ __forceinline__ void hop_epilogue(cx<typename Prec<P>::real> (&acc)[NR][flavours_per_thread<NF>()][12],
                                              const HopProblem &pb, int epi, uint32_t cb, int r0, int fl,
-                                             double (&nrm)[NR], int nts)
+                                             double (&nrm)[NR], int nts, [[maybe_unused]] int res_prec)
 {
     using real = typename Prec<P>::real;
     // the xpay operand and the output, non-temporally where nts asks
@@ -562,6 +564,22 @@ __device__ __forceinline__ void hop_epilogue(cx<typename Prec<P>::real> (&acc)[N
             SpinorIO<P>::template load<0, 12, false>(Rv, pb.out, pb.vh, vec, cb);
 #pragma unroll
         for (int k = 0; k < 12; k++) A[k] = Rv[k] - al * A[k];
+    };
+    [[maybe_unused]] auto residual_out = [&](cx<real> *A, uint32_t vec) {
+        cx<real> C[12];
+        SpinorIO<P>::template load<0, 12, true>(C, pb.res, pb.vh, vec, cb);
+        cx<float> t[12];
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            A[k] = C[k] - A[k];
+            t[k] = mk((float)A[k].re, (float)A[k].im);
+        }
+        if (res_prec == TM_FP32)
+            SpinorIO<TM_FP32>::store(pb.out, pb.vh, vec, cb, t);
+        else if (res_prec == TM_FP16)
+            SpinorIO<TM_FP16>::store(pb.out, pb.vh, vec, cb, t);
+        else
+            SpinorIO<TM_BF16>::store(pb.out, pb.vh, vec, cb, t);
     };
     const real kk = (real)pb.k;
     const uint32_t vh = pb.vh;
@@ -593,8 +611,12 @@ __device__ __forceinline__ void hop_epilogue(cx<typename Prec<P>::real> (&acc)[N
                     for (int k = 0; k < 12; k++) A[k] = T[k];
                 }
             }
-            if (pb.upd) update_out(A, (uint32_t)((r0 + r) * NF + fl), r0 + r);
-            store_out(A, (uint32_t)((r0 + r) * NF + fl));
+            if constexpr (RES) {
+                residual_out(A, (uint32_t)((r0 + r) * NF + fl));
+            } else {
+                if (pb.upd) update_out(A, (uint32_t)((r0 + r) * NF + fl), r0 + r);
+                store_out(A, (uint32_t)((r0 + r) * NF + fl));
+            }
             if (pb.red.op != FIN_NONE) {
                 double s = 0.0;
 #pragma unroll
@@ -630,8 +652,12 @@ __device__ __forceinline__ void hop_epilogue(cx<typename Prec<P>::real> (&acc)[N
             }
 #pragma unroll
             for (int f = 0; f < NF; f++) {
-                if (pb.upd) update_out(A[f], (uint32_t)((r0 + r) * NF + f), r0 + r);
-                store_out(A[f], (uint32_t)((r0 + r) * NF + f));
+                if constexpr (RES) {
+                    residual_out(A[f], (uint32_t)((r0 + r) * NF + f));
+                } else {
+                    if (pb.upd) update_out(A[f], (uint32_t)((r0 + r) * NF + f), r0 + r);
+                    store_out(A[f], (uint32_t)((r0 + r) * NF + f));
+                }
                 if (pb.red.op != FIN_NONE) {
                     double s = 0.0;
 #pragma unroll
@@ -679,7 +705,7 @@ __device__ __forceinline__ bool gated_off(const HopBatch &B)
 // are staged in LDS (FP32, one flavour, one rhs, lexicographic site order);
 // x and y neighbours are then read from there.
 template <int P, int NF, int NR, bool DAG, bool TWL, int RECON, bool LNT, int BS, bool CLV = false,
-          bool LDSS = false>
+          bool LDSS = false, bool RES = false>
 __global__ void __launch_bounds__(BS, (hop_waves<P, NF, NR, CLV, TWL>())) hop_kernel(const HopBatch B)
 {
     using real = typename Prec<P>::real;
@@ -796,7 +822,7 @@ __global__ void __launch_bounds__(BS, (hop_waves<P, NF, NR, CLV, TWL>())) hop_ke
             TM_DIR_FENCE();
         }
 
-        hop_epilogue<P, NF, NR, CLV>(acc, pb, B.epi, cb, r0, fl, nrm, B.nt_streams);
+        hop_epilogue<P, NF, NR, CLV, RES>(acc, pb, B.epi, cb, r0, fl, nrm, B.nt_streams, B.res_prec);
     }
 
     if (pb.red.op != FIN_NONE) {
@@ -819,10 +845,19 @@ __global__ void __launch_bounds__(BS, (hop_waves<P, NF, NR, CLV, TWL>())) hop_ke
     } while (0)
 
 #define TM_HOP_CASE(P, NF, NR, DAG, TWL, RECON, LNT, BS)                                          \
-    if (!clv && !ldss && nf == NF && nr == NR && dagger == DAG && twl == TWL && recon == RECON &&  \
+    if (!clv && !ldss && !res && nf == NF && nr == NR && dagger == DAG && twl == TWL && recon == RECON && \
         lnt == LNT && bs == BS) {                                                                   \
         TM_HOP_RUN((hop_kernel<P, NF, NR, DAG, TWL, RECON, LNT, BS>));                             \
     }
+
+// true residual of a reliable update (FP64, M^+'s last hop, one rhs per thread)
+#define TM_HOP_CASE_RES(P, NF, RECON, LNT, BS)                                                      \
+    if (res && !clv && nf == NF && nr == 1 && dagger == 1 && twl == 0 && recon == RECON && lnt == LNT && \
+        bs == BS) {                                                                                 \
+        TM_HOP_RUN((hop_kernel<P, NF, 1, true, false, RECON, LNT, BS, false, false, true>));        \
+    }
+#define TM_HOP_CASES_RES(P, NF, RECON, BS) \
+    TM_HOP_CASE_RES(P, NF, RECON, true, BS) TM_HOP_CASE_RES(P, NF, RECON, false, BS)
 
 // twisted-clover epilogues (FP64 / FP32, one rhs per thread, no twist-on-load)
 #define TM_HOP_CASE_CLV(P, NF, DAG, RECON, LNT, BS)                                                 \
@@ -862,8 +897,24 @@ __global__ void __launch_bounds__(BS, (hop_waves<P, NF, NR, CLV, TWL>())) hop_ke
     template <>                                                                                \
     hipError_t launch_hop_prec<P>(const HopBatch &B, int nf, int nr, int dagger, int twl,      \
                                   int recon, int bs, bool lnt, unsigned lds, bool clv,         \
-                                  bool ldss, hipStream_t st, hipFuncAttributes *attr)          \
+                                  bool ldss, bool res, hipStream_t st, hipFuncAttributes *attr) \
     {                                                                                          \
+        if constexpr (P == TM_FP64) {                                                          \
+            TM_HOP_CASES_RES(P, 1, 12, 256)                                                    \
+            TM_HOP_CASES_RES(P, 1, 12, 128)                                                    \
+            TM_HOP_CASES_RES(P, 1, 12, 64)                                                     \
+            TM_HOP_CASES_RES(P, 1, 18, 256)                                                    \
+            TM_HOP_CASES_RES(P, 1, 8, 256)                                                     \
+            TM_HOP_CASES_RES(P, 1, 8, 128)                                                     \
+            TM_HOP_CASES_RES(P, 1, 8, 64)                                                      \
+            TM_HOP_CASES_RES(P, 2, 12, 256)                                                    \
+            TM_HOP_CASES_RES(P, 2, 12, 128)                                                    \
+            TM_HOP_CASES_RES(P, 2, 12, 64)                                                     \
+            TM_HOP_CASES_RES(P, 2, 18, 256)                                                    \
+            TM_HOP_CASES_RES(P, 2, 8, 256)                                                     \
+            TM_HOP_CASES_RES(P, 2, 8, 128)                                                     \
+            TM_HOP_CASES_RES(P, 2, 8, 64)                                                      \
+        }                                                                                      \
         if constexpr (P == TM_FP32) {                                                          \
             TM_HOP_CASES_LDSS(P, 256)                                                          \
             TM_HOP_CASES_LDSS(P, 64)                                                           \

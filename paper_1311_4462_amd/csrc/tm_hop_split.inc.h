@@ -19,14 +19,15 @@ namespace twm {
 // One LDS buffer: link products, hop factors (with the site scale in half
 // precision, where each flavour has its own), the element maxima of the
 // half-precision store and the reduction.
-template <int P, int NF>
+template <int P, int NF, bool RES>
 struct SplitLds {
     using real = typename Prec<P>::real;
     static constexpr bool SC = Prec<P>::kScaled;
+    static constexpr bool MX = SC || RES;        // a true residual may be rounded to half precision
     static constexpr int kFac = SC ? NF : 1;
     cx<real> g[8][NF][6][kSplitSites];
     real fac[8][kFac][kSplitSites];
-    float mx[SC ? NF : 1][SC ? 6 : 1][SC ? kSplitSites : 1];
+    float mx[MX ? NF : 1][MX ? 6 : 1][MX ? kSplitSites : 1];
     double red[kSplitThreads / 64];
 };
 
@@ -48,8 +49,8 @@ constexpr bool split_two_buffers()
 // One hop (direction MU, forward or backward) of one site and rhs for all
 // flavours: its link products and factors to LDS.  The link comes in u with
 // several rhs, and is loaded next to the neighbours otherwise.
-template <int P, int NF, bool DAG, bool TWL, int RECON, bool LNT, bool MR, int MU, bool FWD>
-__device__ __forceinline__ void split_hop(SplitLds<P, NF> &sh, cx<typename Prec<P>::real> (&u)[3][3],
+template <int P, int NF, bool DAG, bool TWL, int RECON, bool LNT, bool MR, bool RES, int MU, bool FWD>
+__device__ __forceinline__ void split_hop(SplitLds<P, NF, RES> &sh, cx<typename Prec<P>::real> (&u)[3][3],
                                           const HopProblem &pb, uint32_t nb, uint32_t cb, int rhs,
                                           typename Prec<P>::real sgn, int lane)
 {
@@ -103,7 +104,7 @@ __device__ __forceinline__ void split_hop(SplitLds<P, NF> &sh, cx<typename Prec<
             sh.g[D][f][c][lane] = g[0][c];
             sh.g[D][f][3 + c][lane] = g[1][c];
         }
-        if (f < SplitLds<P, NF>::kFac) sh.fac[D][f][lane] = ((MU == 3) ? (real)2 : (real)1) * (sgn * sc[f]);
+        if (f < SplitLds<P, NF, RES>::kFac) sh.fac[D][f][lane] = ((MU == 3) ? (real)2 : (real)1) * (sgn * sc[f]);
     }
 }
 
@@ -206,12 +207,14 @@ __device__ __forceinline__ void split_finish(const HopBatch &B)
         cg_post(B.post, B.nprob, [&](int i) -> const Reduce & { return B.p[i].red; });
 }
 
-// MR: pb.nrg right-hand sides per block (else one).
-template <int P, int NF, bool DAG, bool TWL, int RECON, bool LNT, bool MR>
+// MR: pb.nrg right-hand sides per block (else one).  RES (FP64): the result
+// becomes the true residual pb.res - A, rounded to precision B.res_prec on its
+// way out; the norm is that of the FP64 values.
+template <int P, int NF, bool DAG, bool TWL, int RECON, bool LNT, bool MR, bool RES = false>
 __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())) hop_split_kernel(const HopBatch B)
 {
     using real = typename Prec<P>::real;
-    using Lds = SplitLds<P, NF>;
+    using Lds = SplitLds<P, NF, RES>;
     extern __shared__ __align__(16) unsigned char split_sh[];
     Lds *const shb = reinterpret_cast<Lds *>(split_sh);
     if (gated_off(B)) return;   // gated launch not needed this iteration
@@ -280,7 +283,7 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
         if constexpr (MR && !split_two_buffers<P>()) __syncthreads();
         if (valid) {
 #define TM_SPLIT_HOP(MU, FWD) \
-    split_hop<P, NF, DAG, TWL, RECON, LNT, MR, MU, FWD>(sh, u, pb, nb, cl, r, sgn, lane)
+    split_hop<P, NF, DAG, TWL, RECON, LNT, MR, RES, MU, FWD>(sh, u, pb, nb, cl, r, sgn, lane)
             switch (wave) {
             case 0: TM_SPLIT_HOP(0, true); break;
             case 1: TM_SPLIT_HOP(0, false); break;
@@ -347,7 +350,13 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
                     for (int e = 0; e < 2; e++) A[f][e] = X[f][e] + kk * A[f][e];
                 if (epi == TM_EPI_TWINV_X_PLUS_KD) twist_pair<real, NF>(A, pb.tw, true);
             }
-            if (pb.upd) {
+            if constexpr (RES) {
+#pragma unroll
+                for (int f = 0; f < NF; f++)
+#pragma unroll
+                    for (int e = 0; e < 2; e++)
+                        A[f][e] = load_elem<P, true>(pb.res, vh, (uint32_t)(r * NF + f), cb, k + 6 * e) - A[f][e];
+            } else if (pb.upd) {
                 // CG residual update: out (holding r) = r - alpha A
                 const real al = (real)pb.upd[r].alpha;
 #pragma unroll
@@ -365,13 +374,14 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
             }
         }
 
-        if constexpr (Lds::SC) {
-            // the site's scale: the maximum over its elements, across the threads
+        // half-precision output: the site's scale is the maximum over its
+        // elements, across the threads
+        if (Lds::SC || (RES && B.res_prec != TM_FP32)) {
             if (act) {
 #pragma unroll
                 for (int f = 0; f < NF; f++)
-                    sh.mx[f][k][site] = fmaxf(fmaxf(fabsf(A[f][0].re), fabsf(A[f][0].im)),
-                                              fmaxf(fabsf(A[f][1].re), fabsf(A[f][1].im)));
+                    sh.mx[f][k][site] = fmaxf(fmaxf(fabsf((float)A[f][0].re), fabsf((float)A[f][0].im)),
+                                              fmaxf(fabsf((float)A[f][1].re), fabsf((float)A[f][1].im)));
             }
             __syncthreads();
         }
@@ -380,7 +390,7 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
             for (int f = 0; f < NF; f++) {
                 const uint32_t vec = (uint32_t)(r * NF + f);
                 [[maybe_unused]] float inv = 0.f;
-                if constexpr (Lds::SC) {
+                if (Lds::SC || (RES && B.res_prec != TM_FP32)) {
                     float m = sh.mx[f][0][site];
 #pragma unroll
                     for (int j = 1; j < 6; j++) m = fmaxf(m, sh.mx[f][j][site]);
@@ -389,10 +399,19 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
                 }
 #pragma unroll
                 for (int e = 0; e < 2; e++) {
-                    if (nts & kNtOut)
+                    if constexpr (RES) {
+                        const cx<float> t = mk((float)A[f][e].re, (float)A[f][e].im);
+                        if (B.res_prec == TM_FP32)
+                            store_elem<TM_FP32, false>(pb.out, vh, vec, cb, k + 6 * e, t, 0.f);
+                        else if (B.res_prec == TM_FP16)
+                            store_elem<TM_FP16, false>(pb.out, vh, vec, cb, k + 6 * e, t, inv);
+                        else
+                            store_elem<TM_BF16, false>(pb.out, vh, vec, cb, k + 6 * e, t, inv);
+                    } else if (nts & kNtOut) {
                         store_elem<P, true>(pb.out, vh, vec, cb, k + 6 * e, A[f][e], inv);
-                    else
+                    } else {
                         store_elem<P, false>(pb.out, vh, vec, cb, k + 6 * e, A[f][e], inv);
+                    }
                 }
             }
         }
@@ -414,23 +433,32 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
     }
 }
 
-#define TM_SPLIT_CASE(P, NF, DAG, TWL, RECON, LNT, MR)                                                 \
-    if (nf == NF && dagger == DAG && twl == TWL && recon == RECON && lnt == LNT && mr == MR) {         \
-        hipLaunchKernelGGL((hop_split_kernel<P, NF, DAG, TWL, RECON, LNT, MR>), dim3(B.total_blocks),  \
-                           dim3(kSplitThreads), (MR && split_two_buffers<P>() ? 2 : 1) * sizeof(SplitLds<P, NF>), st, B);        \
+#define TM_SPLIT_RUN(P, NF, MR, RES, KERNEL)                                                            \
+    do {                                                                                               \
+        constexpr int bufs = MR && split_two_buffers<P>() ? 2 : 1;                                      \
+        hipLaunchKernelGGL((KERNEL), dim3(B.total_blocks), dim3(kSplitThreads),                         \
+                           bufs * sizeof(SplitLds<P, NF, RES>), st, B);                                 \
         return hipGetLastError();                                                                      \
-    }
+    } while (0)
+#define TM_SPLIT_CASE(P, NF, DAG, TWL, RECON, LNT, MR)                                                 \
+    if (!res && nf == NF && dagger == DAG && twl == TWL && recon == RECON && lnt == LNT && mr == MR)   \
+        TM_SPLIT_RUN(P, NF, MR, false, (hop_split_kernel<P, NF, DAG, TWL, RECON, LNT, MR>));
 #define TM_SPLIT_CASES(P, NF, RECON)                                                                \
     TM_SPLIT_CASE(P, NF, 0, 0, RECON, true, false) TM_SPLIT_CASE(P, NF, 1, 0, RECON, true, false)   \
     TM_SPLIT_CASE(P, NF, 0, 0, RECON, false, false) TM_SPLIT_CASE(P, NF, 1, 0, RECON, false, false) \
     TM_SPLIT_CASE(P, NF, 0, 1, RECON, false, false) TM_SPLIT_CASE(P, NF, 1, 1, RECON, false, false)
 #define TM_SPLIT_CASES_MR(P, NF, RECON)                                                            \
     TM_SPLIT_CASE(P, NF, 0, 0, RECON, false, true) TM_SPLIT_CASE(P, NF, 1, 0, RECON, false, true)
+#define TM_SPLIT_CASE_RES(P, NF, RECON, LNT, MR)                                                       \
+    if (res && nf == NF && dagger == 1 && twl == 0 && recon == RECON && lnt == LNT && mr == MR)        \
+        TM_SPLIT_RUN(P, NF, MR, true, (hop_split_kernel<P, NF, true, false, RECON, LNT, MR, true>));
+#define TM_SPLIT_CASES_RES(P, NF, RECON) \
+    TM_SPLIT_CASE_RES(P, NF, RECON, true, false) TM_SPLIT_CASE_RES(P, NF, RECON, false, false)
 
 #define TM_SPLIT_DEFINE(P)                                                                           \
     template <>                                                                                      \
     hipError_t launch_hop_split<P>(const HopBatch &B, int nf, int dagger, int twl, int recon,        \
-                                   bool lnt, bool mr, hipStream_t st)                                \
+                                   bool lnt, bool mr, bool res, hipStream_t st)                      \
     {                                                                                                \
         if (twl || mr) lnt = false;                                                                  \
         TM_SPLIT_CASES(P, 1, 12) TM_SPLIT_CASES(P, 2, 12)                                            \
@@ -438,6 +466,12 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
         TM_SPLIT_CASES(P, 1, 8) TM_SPLIT_CASES(P, 2, 8)                                              \
         if constexpr (P == TM_FP64 || P == TM_FP32) {                                                \
             TM_SPLIT_CASES_MR(P, 1, 12)                                                              \
+        }                                                                                            \
+        if constexpr (P == TM_FP64) {                                                                \
+            TM_SPLIT_CASES_RES(P, 1, 12) TM_SPLIT_CASES_RES(P, 2, 12)                                \
+            TM_SPLIT_CASES_RES(P, 1, 18) TM_SPLIT_CASES_RES(P, 2, 18)                                \
+            TM_SPLIT_CASES_RES(P, 1, 8) TM_SPLIT_CASES_RES(P, 2, 8)                                  \
+            TM_SPLIT_CASE_RES(P, 1, 12, false, true)                                                 \
         }                                                                                            \
         return hipErrorInvalidConfiguration;                                                         \
     }

@@ -1030,6 +1030,7 @@ struct HopProblem {
     // nullable: CG residual update in the epilogue, out = out - alpha A with
     // A the epilogue's result and alpha of each rhs read from here
     const CGScalars *upd;
+    SpinorPtr res;       // HopBatch::res_prec >= 0: out = res - A, out in that precision
     Reduce red;
 };
 
@@ -1041,6 +1042,7 @@ struct HopBatch {
     CGPost post;         // with finish_here
     int finish_here;     // the last block finishes the reductions (direction-split kernel)
     int epi;             // tm_epilogue
+    int res_prec;        // precision of a true residual's output, < 0: none (RES variants)
     int xcd_remap;       // 1: give every XCD a contiguous range of blocks
     int nt_streams;      // kNtOut | kNtX | kNtTime: streams accessed non-temporally
     HopProblem p[kMaxProblems];

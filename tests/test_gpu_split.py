@@ -110,3 +110,30 @@ def test_rule_matches_forced(api, monkeypatch):
     for k in range(n):
         assert rel(outs[n + k], outs[k]) < 1e-14 and rel(outs[2 * n + k], outs[k]) < 1e-14
         assert np.isfinite(outs[k]).all()
+
+
+@pytest.mark.parametrize("split", [0, 1])
+@pytest.mark.parametrize("flavor,recon,pc", [(1, 12, 0), (-1, 18, 1), (2, 12, 1), (2, 8, 0)])
+def test_true_residual_in_the_hop(api, split, flavor, recon, pc, monkeypatch):
+    """Reliable updates take c - M^+ M x from their last hop, rounded to the
+    inner precision: the residual a mixed solve stops on (its last update's
+    norm) is the oracle's, in every inner precision and both kernels."""
+    monkeypatch.setenv("TM_HOP_SPLIT", str(split))
+    c = api.Context()
+    dims = (6, 4, 4, 6)
+    p = api.make_params(dims, 0.15, 0.11, 0.13 if flavor == 2 else 0.0, flavor)
+    op = oparams(p)
+    U = inputs.gauge_field(dims, "near_unit", 341)
+    g = api.Gauge(c, U, p, recon=recon, precs=(0, 1, 2, 3))
+    b = O.project(inputs.gaussian_spinor(dims, op.nf, 342, nrhs=2), dims, 0)
+    tb = to_native(api, c, b, p, 0, 0, 2)
+    for inner in (1, 2, 3):
+        x = api.new_field(p, 0, 2)
+        res = api.tm_cg(c, x, tb, g, pc=pc, tol=1e-10, inner=inner, nrhs=2)
+        xs = from_native(api, c, x, p, 0, 0, 2)
+        for r in range(2):
+            assert res[r]["status"] == 0 and res[r]["reliable_updates"] >= 2
+            assert res[r]["precision_fallbacks"] == 0
+            check_solve(op, U, xs[r], b[r], ("asym", "sym")[pc], res[r]["true_rel_res_normal"])
+    g.close()
+    c.close()

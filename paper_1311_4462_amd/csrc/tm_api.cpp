@@ -2491,7 +2491,7 @@ int tm_force(tm_ctx *ctx, void *F_dev, int force_prec, const void *X_e, const tm
     const size_t fb = spinor_field_bytes(prec, g->vh, g->nf, 1);
     void *Y = workspace(ctx, "force_y", fb, &rc);
     void *Ae = pc == TM_PC_SYM ? workspace(ctx, "force_ae", fb, &rc) : Y;
-    void *Zo = workspace(ctx, "force_z", fb, &rc);
+    void *Zo = odd_tmp(ctx, 0, g, prec, 1, &rc);   // R_oo^-1 D_oe X, left there by Y = M X
     void *Wo = workspace(ctx, "force_w", fb, &rc);
     if (!Y || !Ae || !Zo || !Wo) return rc;
     // Y = M X
@@ -2501,9 +2501,7 @@ int tm_force(tm_ctx *ctx, void *F_dev, int force_prec, const void *X_e, const tm
     if (pc == TM_PC_SYM)
         TM_HIP(ctx, twist_apply(prec, g->nf, sptr(Ae, prec, g->vh, g->nf, 1), sptr(Y, prec, g->vh, g->nf, 1),
                                 g->vh, 1, make_twist(g->p, 1), 1, ctx->stream));
-    // Z_o = R_oo^-1 D_oe X;   W_o = R_oo^-+ (D^+)_oe A_e
-    TM_TRY(hop1(ctx, HopCall{g, prec, 1, 0, 0, TM_EPI_TWINV, X_e, Zo, nullptr, 0.0, 1, FIN_NONE,
-                             nullptr, nullptr}));
+    // W_o = R_oo^-+ (D^+)_oe A_e
     TM_TRY(hop1(ctx, HopCall{g, prec, 1, 1, 0, TM_EPI_TWINV, Ae, Wo, nullptr, 0.0, 1, FIN_NONE,
                              nullptr, nullptr}));
     SpinorPtr A[2] = {sptr(Ae, prec, g->vh, g->nf, 1), sptr(Wo, prec, g->vh, g->nf, 1)};

@@ -1016,7 +1016,8 @@ void *odd_tmp(tm_ctx *ctx, int slot, const tm_gauge *g, int prec, int nrhs, int 
 // Over n problems at once; `fin` reduces |out|^2 per rhs.
 int mat_pc_batch(tm_ctx *ctx, const tm_gauge *const *g, void *const *out, const void *const *in,
                  const int *nrhs, int n, int prec, int pc, int dagger, int fin, CGScalars *const *cg,
-                 bool upd = false, const void *const *res_c = nullptr, int res_prec = 0)
+                 bool upd = false, const void *const *res_c = nullptr, int res_prec = 0,
+                 double *const *red_out = nullptr)
 {
     HopCall k1[kMaxProblems], k2[kMaxProblems];
     for (int i = 0; i < n; i++) {
@@ -1027,7 +1028,7 @@ int mat_pc_batch(tm_ctx *ctx, const tm_gauge *const *g, void *const *out, const 
         k1[i] = HopCall{g[i], prec, 1, dagger, 0, TM_EPI_TWINV, in[i], tmp, nullptr, 0.0, nrhs[i],
                         FIN_NONE, nullptr, nullptr};
         k2[i] = HopCall{g[i], prec, 0, dagger, 0, TM_EPI_RX_PLUS_KD, tmp, out[i], in[i], k2c, nrhs[i],
-                        fin, cg ? cg[i] : nullptr, nullptr, upd ? 1 : 0};
+                        fin, cg ? cg[i] : nullptr, red_out ? red_out[i] : nullptr, upd ? 1 : 0};
         if (pc == TM_PC_SYM) {
             if (!dagger) {
                 k2[i].epi = TM_EPI_X_PLUS_K_TWINV_D;
@@ -1707,40 +1708,65 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         gs[i] = pr[i].g;
         nr[i] = pr[i].nrhs;
     }
-    // c = M^+ b (solution MAT) or c = b (MATDAG_MAT)
+    // Pinned host memory of the whole run, at its largest use (the snapshots)
+    int total_rhs = 0;
+    for (auto &p : pr) total_rhs += p.nrhs;
+    const size_t snap_bytes = (size_t)total_rhs * sizeof(CGScalars) + 4 * sizeof(int);
+    const size_t snap_stride = (snap_bytes + 255) / 256 * 256;
+    char *pinned;
+    {
+        int rc = TM_OK;
+        pinned = (char *)host_scratch(ctx, 2 * snap_stride / sizeof(double), &rc);
+        if (!pinned) return rc;
+    }
+    // c = M^+ b (solution MAT) or c = b (MATDAG_MAT), with |c|^2 and |b|^2 from
+    // one wait
+    std::vector<std::vector<double>> bb(n);
     {
         void *cs[kMaxProblems];
         const void *bs[kMaxProblems];
+        double *out[kMaxProblems];
         for (int i = 0; i < n; i++) {
             cs[i] = pr[i].c;
             bs[i] = pr[i].b;
+            out[i] = pr[i].dres + pr[i].nrhs;
         }
-        if (par->solution == TM_SOLUTION_MATDAG_MAT) {
+        BlasCall nb[kMaxProblems];
+        for (int i = 0; i < n; i++)
+            nb[i] = BlasCall{pr[i].g->vh, pr[i].nrhs, {pr[i].b, nullptr, nullptr, nullptr}, FIN_STORE, nullptr,
+                             pr[i].dres};
+        TM_TRY(launch_blas_batch(ctx, OP_NORM2, TM_FP64, TM_FP64, nf, nb, n));
+        const bool mat = par->solution != TM_SOLUTION_MATDAG_MAT;
+        if (mat) {
+            TM_TRY(mat_pc_batch(ctx, gs, cs, bs, nr, n, TM_FP64, pc, 1, FIN_STORE, nullptr, false, nullptr, 0, out));
+        } else {
             BlasCall cp[kMaxProblems];
             for (int i = 0; i < n; i++)
                 cp[i] = BlasCall{pr[i].g->vh, pr[i].nrhs, {pr[i].b, pr[i].c, nullptr, nullptr}, FIN_NONE,
                                  nullptr, nullptr};
             TM_TRY(launch_blas_batch(ctx, OP_CONVERT, TM_FP64, TM_FP64, nf, cp, n));
-        } else {
-            TM_TRY(mat_pc_batch(ctx, gs, cs, bs, nr, n, TM_FP64, pc, 1, FIN_NONE, nullptr));
         }
-        std::vector<std::vector<double>> cc;
-        TM_TRY(norms_fp64(ctx, pr, cs, cc));
-        for (int i = 0; i < n; i++)
+        double *h = (double *)pinned;
+        for (int i = 0; i < n; i++) {
+            TM_HIP(ctx, hipMemcpyAsync(h, pr[i].dres, (mat ? 2 : 1) * pr[i].nrhs * sizeof(double),
+                                       hipMemcpyDeviceToHost, ctx->stream));
+            h += 2 * pr[i].nrhs;
+        }
+        TM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        h = (double *)pinned;
+        for (int i = 0; i < n; i++) {
+            bb[i].assign(h, h + pr[i].nrhs);
             for (int r = 0; r < pr[i].nrhs; r++) {
-                pr[i].cc[r] = cc[i][r];
-                if (!std::isfinite(cc[i][r])) return fail(ctx, TM_ERR_NAN, "non-finite source norm");
+                pr[i].cc[r] = mat ? h[pr[i].nrhs + r] : h[r];
+                if (!std::isfinite(pr[i].cc[r])) return fail(ctx, TM_ERR_NAN, "non-finite source norm");
             }
+            h += 2 * pr[i].nrhs;
+        }
     }
-    // scalars
+    // scalars (the copy is over before the first snapshot comes back to the
+    // same pinned memory, in stream order)
     {
-        int rc = TM_OK;
-        int total = 0;
-        for (auto &p : pr) total += p.nrhs;
-        double *h = host_scratch(ctx, total * sizeof(CGScalars) / sizeof(double) + 1, &rc);
-        if (!h) return rc;
-        CGScalars *hs = (CGScalars *)h;
-        int off = 0;
+        CGScalars *hs = (CGScalars *)pinned;
         for (int i = 0; i < n; i++) {
             for (int r = 0; r < pr[i].nrhs; r++) {
                 CGScalars s{};
@@ -1748,13 +1774,12 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
                 s.active = pr[i].cc[r] > 0 ? 1 : 0;
                 const double sf = par->stall_factor > 0 ? par->stall_factor : 1.0;
                 s.stall_f2 = sf * sf;
-                hs[off + r] = s;
+                hs[r] = s;
             }
-            TM_HIP(ctx, hipMemcpyAsync(pr[i].cg, hs + off, pr[i].nrhs * sizeof(CGScalars),
-                                       hipMemcpyHostToDevice, ctx->stream));
-            off += pr[i].nrhs;
+            TM_HIP(ctx, hipMemcpyAsync(pr[i].cg, hs, pr[i].nrhs * sizeof(CGScalars), hipMemcpyHostToDevice,
+                                       ctx->stream));
+            hs += pr[i].nrhs;
         }
-        TM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     }
     if (!par->use_x0)
         for (int i = 0; i < n; i++)
@@ -1913,24 +1938,15 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         TM_HIP(ctx, hipGraphInstantiate(&gc.exec, graph, nullptr, nullptr, 0));
     }
 
-    // Host side: chunks of iterations (one graph, or check_every eager
+    // Host side: chunks of iterations (one graph, or up to check_every eager
     // iterations) are enqueued one ahead of the check of the previous chunk,
     // whose scalars and flags come back with one small asynchronous copy into
-    // pinned memory; the chunk enqueued speculatively after convergence runs
-    // gated and does nothing.
-    int total_rhs = 0;
-    for (auto &p : pr) total_rhs += p.nrhs;
-    const size_t snap_bytes = (size_t)total_rhs * sizeof(CGScalars) + 4 * sizeof(int);
-    char *snap[2];
+    // pinned memory.  Iterations past convergence run gated and do nothing,
+    // but cost their launches (4-5 us each), so no chunk is enqueued ahead of
+    // one that should converge, and none larger than what should be left.
+    char *const snap[2] = {pinned, pinned + snap_stride};
     hipEvent_t snap_ev[2] = {nullptr, nullptr};
-    {
-        int rc = TM_OK;
-        double *h = host_scratch(ctx, 2 * ((snap_bytes + 255) / 256) * 256 / sizeof(double), &rc);
-        if (!h) return rc;
-        snap[0] = (char *)h;
-        snap[1] = snap[0] + (snap_bytes + 255) / 256 * 256;
-        for (int k = 0; k < 2; k++) TM_HIP(ctx, hipEventCreateWithFlags(&snap_ev[k], hipEventDisableTiming));
-    }
+    for (int k = 0; k < 2; k++) TM_HIP(ctx, hipEventCreateWithFlags(&snap_ev[k], hipEventDisableTiming));
     struct EvGuard {
         hipEvent_t *e;
         ~EvGuard()
@@ -1940,11 +1956,11 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         }
     } ev_guard{snap_ev};
     const int chunk = gk > 0 ? gk : check_every;
-    auto enqueue_chunk = [&](int slot) -> int {
+    auto enqueue_chunk = [&](int slot, int count) -> int {
         if (gk > 0) {
             TM_HIP(ctx, hipGraphLaunch(gc.exec, ctx->stream));
         } else {
-            for (int k = 0; k < chunk; k++) TM_TRY(iteration());
+            for (int k = 0; k < count; k++) TM_TRY(iteration());
         }
         size_t off = 0;
         for (int i = 0; i < n; i++) {
@@ -1975,22 +1991,48 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
                 if (sc[i][r].active || (mixed && sc[i][r].pending)) return false;
         return true;
     };
+    // Iterations that the rhs of the last snapshot still need, from the rate of
+    // their last eight residuals (chunk: unknown, or no steady decrease).
+    auto left = [&]() -> int {
+        double most = 0.0;
+        for (int i = 0; i < n; i++)
+            for (int r = 0; r < pr[i].nrhs; r++) {
+                const CGScalars &s = sc[i][r];
+                if (!s.active) continue;
+                const int d = std::min(s.niter - 1, 8);
+                if (d < 2) return 2 * chunk;
+                const double rate = std::log(s.hist[(s.niter - 1) % kHistory] / s.hist[(s.niter - 1 - d) % kHistory]) / d;
+                const double need = std::log(s.stop2 / s.rr) / rate;
+                if (!(rate < 0.0) || !(need < 1e6)) return 2 * chunk;
+                most = std::max(most, need);
+            }
+        return (int)std::ceil(most);
+    };
     const int max_stalls = par->max_stalls == 0 ? 3 : par->max_stalls;
     phase.enter("tm_cg: iterations");
     int status = TM_OK;
     bool stalled = false;
     long enqueued = 0;            // iterations enqueued (an upper bound of those run)
     int slot = 0;
-    bool in_flight = false;       // a chunk whose snapshot is not yet read
+    int in_flight = 0;            // iterations of the chunk whose snapshot is not yet read
     for (;;) {
-        bool launched = false;
+        int launched = 0;
         if (enqueued < par->maxiter) {
-            TM_TRY(enqueue_chunk(slot));
-            enqueued += chunk;
-            launched = true;
+            launched = chunk;
+            if (!sc.empty()) {
+                const int after = left() - in_flight;
+                if (in_flight && after <= 0)
+                    launched = 0;
+                else if (gk == 0)
+                    launched = std::min(chunk, std::max(1, after + 1));
+            }
+        }
+        if (launched) {
+            TM_TRY(enqueue_chunk(slot, launched));
+            enqueued += launched;
         }
         if (!in_flight) {
-            // the first chunk: nothing to check yet
+            // nothing to check yet
             in_flight = launched;
             slot ^= 1;
             if (!launched) break;
@@ -2041,23 +2083,29 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
                 if (!done) {
                     // the chunk enqueued above was a no-op: iterate afresh
                     TM_HIP(ctx, launch_start(start, ctx->stream));
-                    launched = false;
-                    in_flight = false;
+                    launched = 0;
+                    in_flight = 0;
                 }
             }
         }
         if (done) break;
-        if (!launched && in_flight && enqueued >= par->maxiter) {
-            status = TM_NOT_CONVERGED;
-            break;
+        if (!launched) {
+            if (in_flight && enqueued >= par->maxiter) {
+                status = TM_NOT_CONVERGED;
+                break;
+            }
+            in_flight = 0;
+            continue;
         }
+        in_flight = launched;
         slot ^= 1;
     }
-    // the last snapshot of the device state (all work enqueued so far done)
+    // A converged run ends on the state it has just read; otherwise the last
+    // state of the device (all work enqueued so far done).
     phase.enter("tm_cg: final residuals");
-    TM_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    TM_TRY(read_scalars(ctx, pr, sc));
-    {
+    if (status != TM_OK || stalled || !all_inactive()) {
+        TM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        TM_TRY(read_scalars(ctx, pr, sc));
         TM_HIP(ctx, hipMemcpyAsync(hflags, flags, sizeof(hflags), hipMemcpyDeviceToHost, ctx->stream));
         TM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     }
@@ -2085,51 +2133,52 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
             }
         return kStalled;
     }
-    TM_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-
-    // reported residuals, recomputed in FP64 from x
-    std::vector<std::vector<double>> rn, rp, bb;
-    {
-        void *r64[kMaxProblems];
-        for (int i = 0; i < n; i++) {
-            int rc = TM_OK;
-            char name[64];
-            snprintf(name, sizeof(name), "cg_rtrue_%d", i);
-            r64[i] = workspace(ctx, name, spinor_field_bytes(TM_FP64, pr[i].g->vh, nf, pr[i].nrhs), &rc);
-            if (!r64[i]) return rc;
+    // reported residuals in FP64 from x: |c - M^+ M x| (rn) and |b - M x| (rp;
+    // MATDAG_MAT: |b - M^+ M x|, the same as the first)
+    std::vector<std::vector<double>> rn(n), rp;
+    const bool mat = par->solution != TM_SOLUTION_MATDAG_MAT;
+    if (true_valid) {
+        // the run's last residual is this x's, and mid = M x of it
+        for (int i = 0; i < n; i++)
+            for (int r = 0; r < pr[i].nrhs; r++) rn[i].push_back(sc[i][r].rr);
+        if (mat && mixed && updates == 0) {
+            // nothing to solve (x is the start): no update has formed M x
+            void *mids[kMaxProblems];
+            const void *xs[kMaxProblems];
+            for (int i = 0; i < n; i++) {
+                mids[i] = pr[i].mid;
+                xs[i] = pr[i].x;
+            }
+            TM_TRY(mat_pc_batch(ctx, gs, mids, xs, nr, n, TM_FP64, pc, 0, FIN_NONE, nullptr));
         }
-        if (true_valid) {
-            // the last step computed the FP64 residual of this x (in the scalars)
-            rn.assign(n, {});
-            for (int i = 0; i < n; i++)
-                for (int r = 0; r < pr[i].nrhs; r++) rn[i].push_back(sc[i][r].rr);
-        } else {
-            TM_TRY(true_residual(ctx, pr, pc, TM_FP64, r64, nullptr, FIN_NONE));
-            TM_TRY(norms_fp64(ctx, pr, r64, rn));
-        }
-        // |b - M x|: y = M x, r = b - y  (MATDAG_MAT: y = M^+ M x, left in y by the
-        // residual above)
+    } else {
         void *ys[kMaxProblems];
-        const void *xs[kMaxProblems];
-        for (int i = 0; i < n; i++) {
-            ys[i] = pr[i].y;
-            xs[i] = pr[i].x;
-        }
-        if (par->solution != TM_SOLUTION_MATDAG_MAT || true_valid)
-            TM_TRY(par->solution != TM_SOLUTION_MATDAG_MAT
-                       ? mat_pc_batch(ctx, gs, ys, xs, nr, n, TM_FP64, pc, 0, FIN_NONE, nullptr)
-                       : normal_op64(ctx, pr, pc, ys, r64, xs));
+        for (int i = 0; i < n; i++) ys[i] = pr[i].y;
+        TM_TRY(true_residual(ctx, pr, pc, TM_FP64, ys, nullptr, FIN_NONE));
+        TM_TRY(norms_fp64(ctx, pr, ys, rn));
+    }
+    if (mat) {
         BlasCall calls[kMaxProblems];
         for (int i = 0; i < n; i++)
-            calls[i] = BlasCall{pr[i].g->vh, pr[i].nrhs, {pr[i].b, pr[i].y, r64[i], nullptr}, FIN_NONE,
-                                nullptr, nullptr};
+            calls[i] = BlasCall{pr[i].g->vh, pr[i].nrhs, {pr[i].b, pr[i].mid, pr[i].y, nullptr}, FIN_STORE,
+                                nullptr, pr[i].dres};
         TM_TRY(launch_blas_batch(ctx, OP_RESIDUAL, TM_FP64, TM_FP64, nf, calls, n));
-        TM_TRY(norms_fp64(ctx, pr, r64, rp));
-        void *bv[kMaxProblems];
-        for (int i = 0; i < n; i++) bv[i] = const_cast<void *>(pr[i].b);
-        TM_TRY(norms_fp64(ctx, pr, bv, bb));
+        double *h = (double *)pinned;
+        for (int i = 0; i < n; i++) {
+            TM_HIP(ctx, hipMemcpyAsync(h, pr[i].dres, pr[i].nrhs * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+            h += pr[i].nrhs;
+        }
+        TM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        h = (double *)pinned;
+        for (int i = 0; i < n; i++) {
+            rp.emplace_back(h, h + pr[i].nrhs);
+            h += pr[i].nrhs;
+        }
+    } else {
+        rp = rn;
+        TM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     }
+    const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     int off = 0;
     for (int i = 0; i < n; i++)
         for (int r = 0; r < pr[i].nrhs; r++, off++) {

@@ -458,14 +458,15 @@ HopCfg default_cfg(const HopCall *calls, int n, int prec, int nf, int twl, int r
     // where the one-thread kernel's fewer LDS passes and waves win: FP32
     // doublet (24^3 x 48 56 / 68 against 61 / 69 tuned, 32^3 x 64 179 / 211
     // against 179 / 205), FP64 (20^3 x 40 38 / 41 against 39 / 43, 24^3 x 48
-    // 79 / 89 against 76 / 86; doublet 24^3 x 48 139 / 159 against 144 / 163,
-    // 32^3 x 64 436 / 498 against 390 / 452), half precision, whose products
+    // 79 / 89 against 76 / 86; doublet 28^3 x 56 239 / 285 against 264 / 294,
+    // 24^3 x 64 with two rhs 306 / 360 against 348 / 386, 32^3 x 64 417 / 493
+    // against 390 / 452), half precision, whose products
     // cross LDS in FP32 (doublet 16^3 x 32 11.4 / 12.7 against 11.8 / 13.3,
     // 20^3 x 40 24 / 28 against 20 / 22; one flavour 16^3 x 32 6.9 / 7.3
     // against 8.0 / 8.7, with two rhs 11 / 11 against 10 / 10).
     const bool shared = nrhs > 1 && nf == 1 && recon == 12 && !twl && !half;   // several rhs per block
     const bool fits = half ? work <= (nf == 2 ? 65536 : 100000)
-                     : prec == TM_FP32 ? nf == 1 || work * nf <= 1L << 20 : shared || work <= 250000L * nf;
+                     : prec == TM_FP32 ? nf == 1 || work * nf <= 1L << 20 : shared || work <= (nf == 1 ? 250000 : twl ? 500000 : 900000);
     if (may_split + (int)fits >= 2) {
         c.bs = kSplitThreads;
         c.split = true;
@@ -616,7 +617,7 @@ int build_hop_batch(tm_ctx *ctx, const HopCall *calls, int n, const HopCfg &cfg,
         hp.nrhs = c.nrhs;
         hp.blk_start = blocks;
         // sites per block
-        const int spb = cfg.split ? kSplitSites : (nf == 2 && kNdSplit) ? cfg.bs / 2 : cfg.bs;
+        const int spb = cfg.split ? split_sites(prec, nf, c.twl != 0) : (nf == 2 && kNdSplit) ? cfg.bs / 2 : cfg.bs;
         hp.nsb = (int)((g->vh + spb - 1) / spb);
         hp.ngrp = (c.nrhs + nr - 1) / nr;
         hp.nrg = nr;

@@ -26,7 +26,7 @@ template <int P>
 hipError_t launch_hop_prec(const HopBatch &B, int nf, int nr, int dagger, int twl, int recon,
                            int bs, bool lnt, unsigned lds, bool clv, bool ldss, bool res, hipStream_t st,
                            hipFuncAttributes *attr = nullptr);
-// Launch the direction-split variant (blocks of kSplitSites sites; mr: several
+// Launch the direction-split variant (blocks of split_sites sites; mr: several
 // rhs per block, 12-real links).
 template <int P>
 hipError_t launch_hop_split(const HopBatch &B, int nf, int dagger, int twl, int recon, bool lnt, bool mr,

@@ -16,18 +16,47 @@
 
 namespace twm {
 
+// Flavours per thread.  FP64 doublets put the two flavours of 32 sites into the
+// halves of a wave (both load the same link), so a block takes the LDS (51 KiB)
+// and the registers of the one-flavour kernel and two blocks share a compute
+// unit where one did: R^-1 D of 12^3 x 24 in a solve 9.5 us against 13.2 with
+// both flavours of 64 sites in a thread, 24^3 x 48 126 against 139.  In FP32,
+// where two blocks fit either way, that costs more addresses and links per
+// block than it gives (20^3 x 40 30 against 28, 12^3 x 24 6.0 against 6.9),
+// half precision gains nothing where this kernel is used, and the twist on load
+// needs both flavours of all twelve elements.
+template <int P, int NF, bool TWL>
+constexpr int split_nl()
+{
+    return split_sites(P, NF, TWL) < kSplitSites ? 1 : NF;
+}
+
+// The value of the lane 32 away (the other flavour of the site).
+__device__ __forceinline__ uint32_t other_half(uint32_t a)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    return (threadIdx.x & 32) ? r[0] : r[1];
+}
+__device__ __forceinline__ float other_half(float a) { return __uint_as_float(other_half(__float_as_uint(a))); }
+__device__ __forceinline__ double other_half(double a)
+{
+    const uint32_t lo = other_half((uint32_t)__double2loint(a)), hi = other_half((uint32_t)__double2hiint(a));
+    return __hiloint2double((int)hi, (int)lo);
+}
+
 // One LDS buffer: link products, hop factors (with the site scale in half
 // precision, where each flavour has its own), the element maxima of the
 // half-precision store and the reduction.
-template <int P, int NF, bool RES>
+template <int P, int NF, bool TWL, bool RES>
 struct SplitLds {
     using real = typename Prec<P>::real;
     static constexpr bool SC = Prec<P>::kScaled;
     static constexpr bool MX = SC || RES;        // a true residual may be rounded to half precision
-    static constexpr int kFac = SC ? NF : 1;
-    cx<real> g[8][NF][6][kSplitSites];
+    static constexpr int NL = split_nl<P, NF, TWL>();
+    static constexpr int kFac = SC ? NL : 1;
+    cx<real> g[8][NL][6][kSplitSites];
     real fac[8][kFac][kSplitSites];
-    float mx[MX ? NF : 1][MX ? 6 : 1][MX ? kSplitSites : 1];
+    float mx[MX ? NL : 1][MX ? 6 : 1][MX ? kSplitSites : 1];
     double red[kSplitThreads / 64];
 };
 
@@ -35,37 +64,45 @@ struct SplitLds {
 template <int P, int NF, bool TWL, bool MR>
 constexpr int split_waves()
 {
-    return P == TM_FP64 && (NF == 2 || TWL) ? 2 : 4;
+    return P == TM_FP64 && (split_nl<P, NF, TWL>() == 2 || TWL) ? 2 : 4;
 }
 // Several rhs: two LDS buffers where they leave room for two blocks per
-// compute unit (the FP64 doublet's takes 99 KiB), else one and a second
-// barrier per rhs.
+// compute unit (FP64's take 51 KiB each), else one and a second barrier per
+// rhs.
 template <int P>
 constexpr bool split_two_buffers()
 {
     return P != TM_FP64;
 }
 
+// Vector (rhs, flavour) of the flavour f a lane holds.
+template <int P, int NF, bool TWL>
+__device__ __forceinline__ uint32_t split_vec(int rhs, int f, int lane)
+{
+    return (uint32_t)(rhs * NF) + (uint32_t)(split_nl<P, NF, TWL>() == NF ? f : lane >> 5);
+}
+
 // One hop (direction MU, forward or backward) of one site and rhs for all
 // flavours: its link products and factors to LDS.  The link comes in u with
 // several rhs, and is loaded next to the neighbours otherwise.
 template <int P, int NF, bool DAG, bool TWL, int RECON, bool LNT, bool MR, bool RES, int MU, bool FWD>
-__device__ __forceinline__ void split_hop(SplitLds<P, NF, RES> &sh, cx<typename Prec<P>::real> (&u)[3][3],
+__device__ __forceinline__ void split_hop(SplitLds<P, NF, TWL, RES> &sh, cx<typename Prec<P>::real> (&u)[3][3],
                                           const HopProblem &pb, uint32_t nb, uint32_t cb, int rhs,
                                           typename Prec<P>::real sgn, int lane)
 {
     using real = typename Prec<P>::real;
+    constexpr int NL = split_nl<P, NF, TWL>();
     constexpr int SIG = (FWD != DAG) ? 1 : -1;   // D: 1 - g forward; D^+ swaps
     constexpr int D = 2 * MU + (FWD ? 0 : 1);
     constexpr bool WORDS = P == TM_FP16 && !TWL;
     constexpr int K0 = (!TWL && MU == 3 && SIG > 0) ? 6 : 0, N = (!TWL && MU == 3) ? 6 : 12;
     const uint32_t vh = pb.vh;
-    [[maybe_unused]] cx<real> v[NF][12];
-    [[maybe_unused]] uint32_t w[NF][12];
-    real sc[NF];
+    [[maybe_unused]] cx<real> v[NL][12];
+    [[maybe_unused]] uint32_t w[NL][12];
+    real sc[NL];
 #pragma unroll
-    for (int f = 0; f < NF; f++) {
-        const uint32_t vec = (uint32_t)(rhs * NF + f);
+    for (int f = 0; f < NL; f++) {
+        const uint32_t vec = split_vec<P, NF, TWL>(rhs, f, lane);
         if constexpr (TWL) {
             SpinorIO<P>::template load<0, 12>(v[f], pb.in, vh, vec, nb);
             sc[f] = (real)1;
@@ -79,7 +116,7 @@ __device__ __forceinline__ void split_hop(SplitLds<P, NF, RES> &sh, cx<typename 
         LinkIO<P, RECON, LNT>::load(u, pb.gauge[FWD ? pb.out_parity : 1 - pb.out_parity], vh, MU, FWD ? cb : nb);
     if constexpr (TWL) apply_twist<real, NF>(v, pb.tw, true);
 #pragma unroll
-    for (int f = 0; f < NF; f++) {
+    for (int f = 0; f < NL; f++) {
         cx<real> g[2][3];
         if constexpr (WORDS) {
             f16x2 u2[3][3], hp[2][3], hs[2][3];
@@ -104,7 +141,7 @@ __device__ __forceinline__ void split_hop(SplitLds<P, NF, RES> &sh, cx<typename 
             sh.g[D][f][c][lane] = g[0][c];
             sh.g[D][f][3 + c][lane] = g[1][c];
         }
-        if (f < SplitLds<P, NF, RES>::kFac) sh.fac[D][f][lane] = ((MU == 3) ? (real)2 : (real)1) * (sgn * sc[f]);
+        if (f < SplitLds<P, NF, TWL, RES>::kFac) sh.fac[D][f][lane] = ((MU == 3) ? (real)2 : (real)1) * (sgn * sc[f]);
     }
 }
 
@@ -140,25 +177,26 @@ __device__ __forceinline__ void store_elem(const SpinorPtr &s, uint32_t vh, uint
 }
 
 // (lo, hi) <- R (lo, hi) or R^-1 (lo, hi) of the element pairs (k, k + 6)
-template <typename T, int NF>
-__device__ __forceinline__ void twist_pair(cx<T> (&v)[NF][2], const Twist &tw, bool inverse)
+template <typename T, int NF, int NL>
+__device__ __forceinline__ void twist_pair(cx<T> (&v)[NL][2], const Twist &tw, bool inverse, int lane)
 {
     const T ta = (T)tw.ta, b = (T)tw.b;
     const T s = inverse ? (T)-1 : (T)1;
     const T c = inverse ? (T)tw.c : (T)1;
-    cx<T> o[NF][2];
+    cx<T> o[NL][2];
 #pragma unroll
-    for (int f = 0; f < NF; f++) {
-        const T t3 = (f == 0) ? ta : -ta;
+    for (int f = 0; f < NL; f++) {
+        const T t3 = (NL == NF ? f == 0 : lane < 32) ? ta : -ta;
 #pragma unroll
         for (int e = 0; e < 2; e++) {
             cx<T> r = v[f][e] + (s * t3) * times_i(v[f][1 - e]);
-            if constexpr (NF == 2) r = r + (s * b) * v[1 - f][e];
+            if constexpr (NL == 2) r = r + (s * b) * v[1 - f][e];
+            if constexpr (NL < NF) r = r + (s * b) * mk(other_half(v[f][e].re), other_half(v[f][e].im));
             o[f][e] = c * r;
         }
     }
 #pragma unroll
-    for (int f = 0; f < NF; f++)
+    for (int f = 0; f < NL; f++)
 #pragma unroll
         for (int e = 0; e < 2; e++) v[f][e] = o[f][e];
 }
@@ -214,7 +252,8 @@ template <int P, int NF, bool DAG, bool TWL, int RECON, bool LNT, bool MR, bool 
 __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())) hop_split_kernel(const HopBatch B)
 {
     using real = typename Prec<P>::real;
-    using Lds = SplitLds<P, NF, RES>;
+    using Lds = SplitLds<P, NF, TWL, RES>;
+    constexpr int NL = Lds::NL, NS = split_sites(P, NF, TWL);
     extern __shared__ __align__(16) unsigned char split_sh[];
     Lds *const shb = reinterpret_cast<Lds *>(split_sh);
     if (gated_off(B)) return;   // gated launch not needed this iteration
@@ -236,7 +275,7 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
     // the hop of this wave: neighbour, link (U, or U^+ for a backward hop) and factor
     const int mu = wave >> 1;
     const bool fwd = (wave & 1) == 0;
-    const uint32_t jl = (uint32_t)sb * kSplitSites + lane;
+    const uint32_t jl = (uint32_t)sb * NS + (lane & (NS - 1));
     const bool valid = jl < vh;
     uint32_t nb = 0, cl = 0;
     real sgn = (real)1;
@@ -267,12 +306,13 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
     int k, site;
     if constexpr (P == TM_FP32) {
         k = (int)(threadIdx.x >> 7) * 2 + (int)(threadIdx.x & 1);
-        site = (int)(threadIdx.x & 127) >> 1;
+        site = NL == NF ? (int)(threadIdx.x & 127) >> 1
+                        : (lane & 32) | (int)(threadIdx.x & 64) >> 2 | (lane & 31) >> 1;
     } else {
         k = wave;
         site = lane;
     }
-    const uint32_t je = (uint32_t)sb * kSplitSites + site;
+    const uint32_t je = (uint32_t)sb * NS + (site & (NS - 1));
     const bool act = k < 6 && je < vh;
     const uint32_t cb = act ? site_of(pb, je) : 0;
     const int s = k >= 3, c = k - 3 * s;
@@ -299,10 +339,10 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
         __syncthreads();
 
         double nrm = 0.0;
-        cx<real> A[NF][2];
+        cx<real> A[NL][2];
         if (act) {
 #pragma unroll
-            for (int f = 0; f < NF; f++) {
+            for (int f = 0; f < NL; f++) {
                 cx<real> lo = mk((real)0, (real)0), hi = mk((real)0, (real)0);
 #pragma unroll
                 for (int d = 0; d < 8; d++) {
@@ -334,40 +374,40 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
             }
             const int epi = B.epi;
             const real kk = (real)pb.k;
-            if (epi == TM_EPI_TWINV || epi == TM_EPI_X_PLUS_K_TWINV_D) twist_pair<real, NF>(A, pb.tw, true);
+            if (epi == TM_EPI_TWINV || epi == TM_EPI_X_PLUS_K_TWINV_D) twist_pair<real, NF>(A, pb.tw, true, lane);
             if (epi >= TM_EPI_RX_PLUS_KD) {
-                cx<real> X[NF][2];
+                cx<real> X[NL][2];
 #pragma unroll
-                for (int f = 0; f < NF; f++)
+                for (int f = 0; f < NL; f++)
 #pragma unroll
                     for (int e = 0; e < 2; e++)
-                        X[f][e] = (nts & kNtX) ? load_elem<P, true>(pb.x, vh, (uint32_t)(r * NF + f), cb, k + 6 * e)
-                                               : load_elem<P, false>(pb.x, vh, (uint32_t)(r * NF + f), cb, k + 6 * e);
-                if (epi == TM_EPI_RX_PLUS_KD) twist_pair<real, NF>(X, pb.tw, false);
+                        X[f][e] = (nts & kNtX) ? load_elem<P, true>(pb.x, vh, split_vec<P, NF, TWL>(r, f, lane), cb, k + 6 * e)
+                                               : load_elem<P, false>(pb.x, vh, split_vec<P, NF, TWL>(r, f, lane), cb, k + 6 * e);
+                if (epi == TM_EPI_RX_PLUS_KD) twist_pair<real, NF>(X, pb.tw, false, lane);
 #pragma unroll
-                for (int f = 0; f < NF; f++)
+                for (int f = 0; f < NL; f++)
 #pragma unroll
                     for (int e = 0; e < 2; e++) A[f][e] = X[f][e] + kk * A[f][e];
-                if (epi == TM_EPI_TWINV_X_PLUS_KD) twist_pair<real, NF>(A, pb.tw, true);
+                if (epi == TM_EPI_TWINV_X_PLUS_KD) twist_pair<real, NF>(A, pb.tw, true, lane);
             }
             if constexpr (RES) {
 #pragma unroll
-                for (int f = 0; f < NF; f++)
+                for (int f = 0; f < NL; f++)
 #pragma unroll
                     for (int e = 0; e < 2; e++)
-                        A[f][e] = load_elem<P, true>(pb.res, vh, (uint32_t)(r * NF + f), cb, k + 6 * e) - A[f][e];
+                        A[f][e] = load_elem<P, true>(pb.res, vh, split_vec<P, NF, TWL>(r, f, lane), cb, k + 6 * e) - A[f][e];
             } else if (pb.upd) {
                 // CG residual update: out (holding r) = r - alpha A
                 const real al = (real)pb.upd[r].alpha;
 #pragma unroll
-                for (int f = 0; f < NF; f++)
+                for (int f = 0; f < NL; f++)
 #pragma unroll
                     for (int e = 0; e < 2; e++)
-                        A[f][e] = load_elem<P, false>(pb.out, vh, (uint32_t)(r * NF + f), cb, k + 6 * e) - al * A[f][e];
+                        A[f][e] = load_elem<P, false>(pb.out, vh, split_vec<P, NF, TWL>(r, f, lane), cb, k + 6 * e) - al * A[f][e];
             }
             if (pb.red.op != FIN_NONE) {
 #pragma unroll
-                for (int f = 0; f < NF; f++)
+                for (int f = 0; f < NL; f++)
 #pragma unroll
                     for (int e = 0; e < 2; e++)
                         nrm += (double)A[f][e].re * A[f][e].re + (double)A[f][e].im * A[f][e].im;
@@ -379,7 +419,7 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
         if (Lds::SC || (RES && B.res_prec != TM_FP32)) {
             if (act) {
 #pragma unroll
-                for (int f = 0; f < NF; f++)
+                for (int f = 0; f < NL; f++)
                     sh.mx[f][k][site] = fmaxf(fmaxf(fabsf((float)A[f][0].re), fabsf((float)A[f][0].im)),
                                               fmaxf(fabsf((float)A[f][1].re), fabsf((float)A[f][1].im)));
             }
@@ -387,8 +427,8 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
         }
         if (act) {
 #pragma unroll
-            for (int f = 0; f < NF; f++) {
-                const uint32_t vec = (uint32_t)(r * NF + f);
+            for (int f = 0; f < NL; f++) {
+                const uint32_t vec = split_vec<P, NF, TWL>(r, f, lane);
                 [[maybe_unused]] float inv = 0.f;
                 if (Lds::SC || (RES && B.res_prec != TM_FP32)) {
                     float m = sh.mx[f][0][site];
@@ -433,16 +473,16 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
     }
 }
 
-#define TM_SPLIT_RUN(P, NF, MR, RES, KERNEL)                                                            \
+#define TM_SPLIT_RUN(P, NF, TWL, MR, RES, KERNEL)                                                            \
     do {                                                                                               \
         constexpr int bufs = MR && split_two_buffers<P>() ? 2 : 1;                                      \
         hipLaunchKernelGGL((KERNEL), dim3(B.total_blocks), dim3(kSplitThreads),                         \
-                           bufs * sizeof(SplitLds<P, NF, RES>), st, B);                                 \
+                           bufs * sizeof(SplitLds<P, NF, TWL, RES>), st, B);                                 \
         return hipGetLastError();                                                                      \
     } while (0)
 #define TM_SPLIT_CASE(P, NF, DAG, TWL, RECON, LNT, MR)                                                 \
     if (!res && nf == NF && dagger == DAG && twl == TWL && recon == RECON && lnt == LNT && mr == MR)   \
-        TM_SPLIT_RUN(P, NF, MR, false, (hop_split_kernel<P, NF, DAG, TWL, RECON, LNT, MR>));
+        TM_SPLIT_RUN(P, NF, TWL, MR, false, (hop_split_kernel<P, NF, DAG, TWL, RECON, LNT, MR>));
 #define TM_SPLIT_CASES(P, NF, RECON)                                                                \
     TM_SPLIT_CASE(P, NF, 0, 0, RECON, true, false) TM_SPLIT_CASE(P, NF, 1, 0, RECON, true, false)   \
     TM_SPLIT_CASE(P, NF, 0, 0, RECON, false, false) TM_SPLIT_CASE(P, NF, 1, 0, RECON, false, false) \
@@ -451,7 +491,7 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
     TM_SPLIT_CASE(P, NF, 0, 0, RECON, false, true) TM_SPLIT_CASE(P, NF, 1, 0, RECON, false, true)
 #define TM_SPLIT_CASE_RES(P, NF, RECON, LNT, MR)                                                       \
     if (res && nf == NF && dagger == 1 && twl == 0 && recon == RECON && lnt == LNT && mr == MR)        \
-        TM_SPLIT_RUN(P, NF, MR, true, (hop_split_kernel<P, NF, true, false, RECON, LNT, MR, true>));
+        TM_SPLIT_RUN(P, NF, false, MR, true, (hop_split_kernel<P, NF, true, false, RECON, LNT, MR, true>));
 #define TM_SPLIT_CASES_RES(P, NF, RECON) \
     TM_SPLIT_CASE_RES(P, NF, RECON, true, false) TM_SPLIT_CASE_RES(P, NF, RECON, false, false)
 

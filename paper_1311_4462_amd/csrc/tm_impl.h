@@ -20,9 +20,15 @@ constexpr int kMaxProblems = 8;   // problems per batched launch
 #endif
 constexpr bool kNdSplit = TM_ND_SPLIT != 0;
 constexpr int kBlock = 256;       // default threads per block
-// direction-split hop kernel: sites of a block, and its threads (one wave per hop)
+// direction-split hop kernel: lanes of a wave, threads of a block (a wave per
+// hop) and sites of a block (half as many where the halves of a wave hold the
+// two flavours of a doublet)
 constexpr int kSplitSites = 64;
 constexpr int kSplitThreads = 8 * kSplitSites;
+constexpr int split_sites(int prec, int nf, bool twl)
+{
+    return nf == 2 && prec == TM_FP64 && !twl ? kSplitSites / 2 : kSplitSites;
+}
 // Device scratch of the allocation-free operator call: 256 MiB per GPU
 // (the odd temporary of the 32^3 x 64 FP32 doublet operator is 192 MiB).
 constexpr size_t kNoAllocScratchBytes = (size_t)256 << 20;

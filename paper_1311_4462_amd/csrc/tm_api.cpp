@@ -897,11 +897,15 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
     TM_TRY(build_hop_batch(ctx, calls, n, cfg, &B));
     TM_TRY(hop_lds_plan(ctx, B, prec, nf, cfg.nr, dagger, twl, recon, cfg, clv, &lds));
     // A small launch of the direction-split kernel finishes its reductions
-    // itself, while the blocks' counts on one address take less than the
-    // finish launch: FP64 CG at 8^3 x 16 (64 blocks) 2100 -> 1990 us, at
-    // 12^3 x 24 (324 blocks) 2760 -> 2880.
+    // itself: its counts and loads across the XCDs take about 2 us where the
+    // finish launch takes 4.5 (FP64 CG at 8^3 x 16, 64 blocks: 2100 -> 1990
+    // us), with more blocks as long as the finish launch.  Mixed solves, whose
+    // 13 launches an iteration the host enqueues no faster than they run, gain
+    // by the launch itself (16^3 x 32 FP32 4290 -> 3880 us, 12^3 x 24 FP16
+    // 3310 -> 3000; FP64 CG of the doublet at 16^3 x 32 9690 -> 9950).
     B.post = ctx->post;
-    B.finish_here = cfg.split && calls[0].fin != FIN_NONE && ctx->post.flags && B.total_blocks <= 64;
+    B.finish_here = cfg.split && calls[0].fin != FIN_NONE && ctx->post.flags &&
+                    B.total_blocks <= (ctx->post.mixed ? kFinishGroup * kFinishGroups : kFinishGroup);
     B.gate_copy = ctx->gate_copy;
     TM_HIP(ctx, dispatch_hop(B, prec, nf, cfg.nr, dagger, twl, recon, cfg, clv, lds, ctx->stream));
     if (ctx->gate_copy) {
@@ -1871,9 +1875,9 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
     CGFlags *flags = nullptr;
     {
         int rc = TM_OK;
-        flags = (CGFlags *)workspace(ctx, "cg_flags", 256, &rc);
+        flags = (CGFlags *)workspace(ctx, "cg_flags", sizeof(CGFlags), &rc);
         if (!flags) return rc;
-        TM_HIP(ctx, hipMemsetAsync(flags, 0, 256, ctx->stream));
+        TM_HIP(ctx, hipMemsetAsync(flags, 0, sizeof(CGFlags), ctx->stream));
     }
     FinishBatch start;
     memset(&start, 0, sizeof(start));

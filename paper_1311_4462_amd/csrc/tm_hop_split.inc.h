@@ -212,33 +212,61 @@ __device__ __forceinline__ void partial_put(double *p, double s)
     __asm__ volatile("" : "+v"(old)::"memory");
 }
 
-// The reductions of a small launch by its last block, a wave per vector: saves
-// the finish launch (4.5-5 us in a CG iteration) for about 2 us at the end of
-// the hop.
+// The reductions of a launch by its last block, in place of the finish launch.
+// The blocks count themselves in groups of up to 64, the last of each group
+// among the groups, so that no address takes more than 64 atomics; a wave or
+// several add the partials of a vector, four loads of a lane in flight.
 __device__ __forceinline__ void split_finish(const HopBatch &B)
 {
     __shared__ int last;
+    __shared__ double sums[8];
     if (threadIdx.x == 0) {
-        int *const done = &B.post.flags->done;
-        last = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == B.total_blocks - 1;
-        if (last) *done = 0;
+        CGFlags &f = *B.post.flags;
+        const int ng = (B.total_blocks + kFinishGroup - 1) / kFinishGroup;
+        const int g = ng == 1 ? 0 : (int)blockIdx.x % ng;
+        const int size = ng == 1 ? B.total_blocks : B.total_blocks / ng + (g < B.total_blocks % ng);
+        int *const done = &f.done_grp[g].n;
+        last = 0;
+        if (__hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == size - 1) {
+            *done = 0;
+            last = ng == 1 || __hip_atomic_fetch_add(&f.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ng - 1;
+            if (last) f.done = 0;
+        }
     }
     __syncthreads();
     if (!last) return;
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-    int k = 0;
-    for (int i = 0; i < B.nprob; i++) {
-        const Reduce &rd = B.p[i].red;
-        for (int v = 0; v < rd.nvec; v++, k++) {
-            if ((k & 7) != wave) continue;
-            double s = 0.0;
-            for (int b = lane; b < rd.nblk; b += 64)
-                s += __longlong_as_double((long long)__hip_atomic_load(
-                    (unsigned long long *)&rd.partials[(long)v * rd.nblk + b], __ATOMIC_RELAXED,
-                    __HIP_MEMORY_SCOPE_AGENT));
-            s = wave_sum(s);
-            if (lane == 0) finish_apply(rd, v, s);
+    int nv = 0;
+    for (int i = 0; i < B.nprob; i++) nv += B.p[i].red.nvec;
+    // waves per vector
+    const int wpv = B.total_blocks <= kFinishGroup || nv > 4 ? 1 : nv > 2 ? 2 : nv == 2 ? 4 : 8;
+    const int sub = wave % wpv;
+    for (int k0 = 0; k0 < nv; k0 += 8 / wpv) {
+        int i = 0, v = k0 + wave / wpv;
+        while (i < B.nprob && v >= B.p[i].red.nvec) v -= B.p[i++].red.nvec;
+        double s = 0.0;
+        if (i < B.nprob) {
+            const Reduce &rd = B.p[i].red;
+            for (int b0 = sub * 64 + lane; b0 < rd.nblk; b0 += wpv * 256) {
+                double a[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int b = b0 + j * wpv * 64;
+                    a[j] = b < rd.nblk ? __longlong_as_double((long long)__hip_atomic_load(
+                                             (unsigned long long *)&rd.partials[(long)v * rd.nblk + b],
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                                       : 0.0;
+                }
+                s += (a[0] + a[1]) + (a[2] + a[3]);
+            }
         }
+        s = wave_sum(s);
+        if (wpv > 1) {   // one pass
+            if (lane == 0) sums[wave] = s;
+            __syncthreads();
+            for (int w = 1; w < wpv && sub == 0; w++) s += sums[wave + w];
+        }
+        if (lane == 0 && sub == 0 && i < B.nprob) finish_apply(B.p[i].red, v, s);
     }
     __syncthreads();
     if (B.p[0].red.op == FIN_BETA || B.p[0].red.op == FIN_RELIABLE)

@@ -849,6 +849,7 @@ struct Reduce {
 // A launch of an iteration is gated by a flag here, so iterations enqueued past
 // convergence (the rest of a captured graph or of a host check period) do
 // nothing.
+constexpr int kFinishGroup = 64, kFinishGroups = 32;
 struct CGFlags {
     int update;      // the reliable update of this iteration runs (mixed)
     int updates;     // reliable updates decided (for reporting)
@@ -856,8 +857,12 @@ struct CGFlags {
     int iters;       // iterations that ran
     int ran;         // this iteration runs: its first launch copies `run` here, the others
                      // are gated by the copy, since `run` is set anew before the last of them
-    int done;        // blocks that have left their partials (launches that finish their own reduction)
-    int done_fin;    // the same for the blocks of the finish kernel
+    int done;        // groups of blocks that have left their partials (launches that finish their
+                     // own reduction)
+    int done_fin;    // blocks of the finish kernel that have finished their vectors
+    struct alignas(128) {
+        int n;       // blocks of a group, each count in a cache line of its own
+    } done_grp[kFinishGroups];
 };
 
 // What follows the reductions of an iteration's last hop (FIN_BETA) and of a

@@ -137,3 +137,25 @@ def test_true_residual_in_the_hop(api, split, flavor, recon, pc, monkeypatch):
             check_solve(op, U, xs[r], b[r], ("asym", "sym")[pc], res[r]["true_rel_res_normal"])
     g.close()
     c.close()
+
+
+# vectors the last block of a launch finishes: by eight, four, two waves each,
+# and by a wave each in two passes; 80 to 720 blocks in groups of up to 64
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 9])
+def test_finish_in_the_hop(api, nrhs):
+    """A mixed solve whose launches count their blocks in several groups: the
+    residual it reports from its own reductions is that of its solution."""
+    dims = (8, 8, 8, 20)
+    c = api.Context()
+    p = api.make_params(dims, 0.15, 0.1, 0.0, 1)
+    U = inputs.gauge_field(dims, "haar", 341)
+    g = api.Gauge(c, U, p, precs=(0, 1))
+    b = O.project(inputs.gaussian_spinor(dims, 1, 342, nrhs=nrhs), dims, 0)
+    x = api.new_field(p, 0, nrhs)
+    res = api.tm_cg(c, x, to_native(api, c, b, p, 0, 0, nrhs), g, tol=1e-10, inner=1, nrhs=nrhs)
+    xs = from_native(api, c, x, p, 0, 0, nrhs)
+    for r in {0, nrhs - 1}:
+        assert res[r]["status"] == 0 and res[r]["reliable_updates"] > 0
+        check_solve(oparams(p), U, xs[r], b[r], "asym", res[r]["true_rel_res_normal"])
+    g.close()
+    c.close()

@@ -1886,7 +1886,7 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         start.r[i].cg = pr[i].cg;
         start.r[i].nvec = pr[i].nrhs;
     }
-    start.post = CGPost{flags, delta * delta, mixed ? 1 : 0, par->maxiter};
+    start.post = CGPost{flags, delta * delta, mixed ? 1 : 0, par->maxiter, 1};
 
     // Tune every hop the iterations launch before any launch is gated or
     // captured (the tuner times real launches and is skipped in both cases):
@@ -1909,12 +1909,25 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
     }
 
     TM_HIP(ctx, launch_start(start, ctx->stream));
-    auto iteration = [&]() -> int {
+    // The launches of a reliable update follow every fourth iteration in FP32,
+    // every second in FP16 and each in BF16, and the last of a chunk: gated off
+    // they cost 4-5 us each, 22 of the 79 us of a 16^3 x 32 FP32 iteration, and
+    // updates come once in 6-17 iterations.  The residual of FP32 still falls
+    // after the update was due, so no iteration is lost (16^3 x 32 4115 us with
+    // launches in each, 3695 in every second, 3440 in every fourth; 24^3 x 48
+    // 12030 / 11680 / 11530).  FP16 loses some from the third on (32^3 x 64
+    // doublet, kappa 0.15: 170 iterations, 170, 182, 187; 120.3 ms, 119.1,
+    // 126.2, 128.9), BF16 from the second (12^3 x 24, kappa 0.15: 104, 116,
+    // 115, 156).
+    const int update_every = inner == TM_FP32 ? 4 : inner == TM_FP16 ? 2 : 1;
+    auto iteration = [&](int k, int count) -> int {
+        const bool upd = k % update_every == update_every - 1 || k == count - 1;
         ctx->post = start.post;
+        ctx->post.may_update = upd;
         ctx->gate = &flags->run;
         ctx->gate_copy = &flags->ran;
         int rc = iteration_core();
-        if (rc == TM_OK && mixed) {
+        if (rc == TM_OK && mixed && upd) {
             ctx->gate = &flags->update;
             rc = reliable_update();
             ctx->gate = &flags->ran;
@@ -1931,7 +1944,7 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
     if (gk > 0) {
         TM_HIP(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
         int rc = TM_OK;
-        for (int k = 0; k < gk && rc == TM_OK; k++) rc = iteration();
+        for (int k = 0; k < gk && rc == TM_OK; k++) rc = iteration(k, gk);
         hipGraph_t graph = nullptr;
         hipError_t e = hipStreamEndCapture(ctx->stream, &graph);
         if (rc != TM_OK) {
@@ -1965,7 +1978,7 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         if (gk > 0) {
             TM_HIP(ctx, hipGraphLaunch(gc.exec, ctx->stream));
         } else {
-            for (int k = 0; k < count; k++) TM_TRY(iteration());
+            for (int k = 0; k < count; k++) TM_TRY(iteration(k, count));
         }
         size_t off = 0;
         for (int i = 0; i < n; i++) {

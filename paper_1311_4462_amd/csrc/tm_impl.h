@@ -871,12 +871,17 @@ struct CGFlags {
 // whose rr fell below delta^2 maxrr, or any rhs whose iterated residual
 // converged and awaits verification).  After either: the next iteration runs
 // while some rhs is active (mixed: or awaits its verifying update) and fewer
-// than maxiter have run.
+// than maxiter have run.  An iteration enqueued without the launches of an
+// update (may_update 0) leaves it to the next, which iterates first, unless
+// nothing is left to iterate: then its own step (the launch gated by `ran`)
+// waits as well, the next iteration's hops are gated off, and its update takes
+// the state as an update of this iteration would have.
 struct CGPost {
     CGFlags *flags;        // null: no flags to set
     double delta2;
     int mixed;
     int maxiter;
+    int may_update;        // the launches of a reliable update follow this iteration's
 };
 
 struct FinishBatch {
@@ -934,7 +939,10 @@ __device__ __forceinline__ void finish_apply(const Reduce &rd, int v, double s)
                 c.pending = 1;
             }
         } else {
+            // converged, or pending since an iteration without an update:
+            // its step is in x already, and an update restarts from r
             c.beta = 0.0;
+            c.rr_old = 0.0;
         }
     } else if (rd.op == FIN_RELIABLE) {
         // the residual was replaced by the true one (reliable update):
@@ -978,27 +986,34 @@ __device__ __forceinline__ void finish_apply(const Reduce &rd, int v, double s)
 template <typename F>
 __device__ __forceinline__ void cg_post(const CGPost &P, int nprob, const F &reduce)
 {
-    int live = 0, need = 0;
+    int act = 0, live = 0, need = 0;
     for (int i = 0; i < nprob; i++) {
         const Reduce &rd = reduce(i);
         for (int r = (int)threadIdx.x; r < rd.nvec; r += (int)blockDim.x) {
             const CGScalars &c = rd.cg[r];
+            if (c.active) act = 1;
             if (c.active || (P.mixed && c.pending)) live = 1;
             if (c.pending || (c.active && c.rr < P.delta2 * c.maxrr)) need = 1;
         }
     }
+    act = __syncthreads_or(act);
     live = __syncthreads_or(live);
     need = __syncthreads_or(need);
     if (threadIdx.x == 0) {
         CGFlags &f = *P.flags;
         if (reduce(0).op == FIN_BETA) {
             f.iters += 1;
-            f.update = (P.mixed && need) ? 1 : 0;
+            // whether the iteration loop itself goes on
+            const bool more = act && f.iters < P.maxiter;
+            f.update = (P.mixed && need && (P.may_update || !more)) ? 1 : 0;
             f.updates += f.update;
+            if (f.update && !P.may_update) f.ran = 0;
+            f.run = ((P.may_update ? live : act) && f.iters < P.maxiter) ? 1 : 0;
         } else {
             f.update = 0;
+            f.ran = 1;
+            f.run = (live && f.iters < P.maxiter) ? 1 : 0;
         }
-        f.run = (live && f.iters < P.maxiter) ? 1 : 0;
     }
 }
 

@@ -8,7 +8,8 @@ import pytest
 from oracle import oracle as O
 from paper_1311_4462_amd import inputs
 
-from .gpu_util import TOL, check_solve, from_native, oparams, oracle_dslash, rel, to_native
+from .gpu_util import (TOL, check_solve, from_native, oparams, oracle_dslash, oracle_normal_residual, rel,
+                       to_native)
 
 pytestmark = pytest.mark.gpu
 
@@ -157,5 +158,37 @@ def test_finish_in_the_hop(api, nrhs):
     for r in {0, nrhs - 1}:
         assert res[r]["status"] == 0 and res[r]["reliable_updates"] > 0
         check_solve(oparams(p), U, xs[r], b[r], "asym", res[r]["true_rel_res_normal"])
+    g.close()
+    c.close()
+
+
+# a reliable update is due in iterations with and without the launches for it,
+# in the last ones allowed, and for one right-hand side while another iterates
+@pytest.mark.parametrize("inner", [1, 2, 3])
+@pytest.mark.parametrize("graph,check", [(0, 0), (0, 3), (3, 0), (5, 0)])
+def test_updates_between_iterations(api, inner, graph, check):
+    """Whatever iteration a mixed solve ends on, the residual it reports is that
+    of its solution; a free run converges."""
+    dims, nrhs = (4, 4, 4, 6), 3
+    c = api.Context()
+    p = api.make_params(dims, 0.12, 0.1, 0.0, 1)
+    U = inputs.gauge_field(dims, "haar", 351)
+    g = api.Gauge(c, U, p, precs=(0, inner))
+    b = O.project(inputs.gaussian_spinor(dims, 1, 352, nrhs=nrhs), dims, 0)
+    b[1] = 0.0                       # converged from the start
+    b[2].reshape(-1, 12)[1:] = 0.0   # a point source
+    tb = to_native(api, c, b, p, 0, 0, nrhs)
+    x = api.new_field(p, 0, nrhs)
+    for m in (*range(1, 10), 500):
+        res = api.tm_cg(c, x, tb, g, tol=1e-10, inner=inner, nrhs=nrhs, maxiter=m, graph_iters=graph,
+                        check_every=check)
+        xs = from_native(api, c, x, p, 0, 0, nrhs)
+        assert not xs[1].any()
+        assert m == 500 or res[0]["iters"] <= m
+        for r in (0, 2):
+            v = oracle_normal_residual(oparams(p), U, xs[r], b[r], "asym")
+            assert abs(v - res[r]["true_rel_res_normal"]) <= 1e-3 * v, (m, r, v, res[r])
+            if m == 500:
+                assert res[r]["status"] == 0 and v <= 1.0000001e-10, (r, v)
     g.close()
     c.close()

@@ -393,21 +393,24 @@ std::vector<HopCfg> cfg_candidates(int prec, int nf, int nr, int twl, int recon,
 // flavour, 12-real links): the links are loaded once per block, so more is
 // better until the blocks no longer fill the chip evenly.  `slots` blocks run
 // at once (three per compute unit in FP32, four of the single-rhs kernel with
-// its one LDS buffer, two in FP64); a block's
-// time is about its rhs and 1.5 more for the links and the start, and the
-// launch takes the rounds its blocks need.  16^3 x 32 FP32, 12 rhs, R^-1 D:
-// 1 / 2 / 3 / 4 / 6 / 12 per block 65 / 57 / 54 / 51 / 49 / 53 us (four per
-// thread of the one-thread kernel: 90).
+// its one LDS buffer, two in FP64; FP64 with one rhs behaves like three while
+// the launch is small and its links stay in L2); a block's time is about its
+// rhs and 1.5 more for the links and the start, and the launch takes the
+// rounds its blocks need.  16^3 x 32 FP32, 12 rhs, R^-1 D: 1 / 2 / 3 / 4 / 6 /
+// 12 per block 65 / 57 / 54 / 51 / 49 / 53 us (four per thread of the
+// one-thread kernel: 90).  FP64 CG, us: 12^3 x 24 with four rhs 2305 / 2398 /
+// 2866 / 2508 by 1 / 2 / 3 / 4, 16^3 x 32 5548 / 5305 / 6312 / 5117, with
+// twelve 17270 by 1, 14500 by 6 and 13900 by 12.
 int split_group(const HopCall *calls, int n, int prec)
 {
     int most = 1, best = 1;
     for (int i = 0; i < n; i++) most = std::max(most, calls[i].nrhs);
     double t_best = 1e30;
     for (int q = 1; q <= std::min(most, 12); q++) {
-        const long slots = prec == TM_FP64 ? 512 : q == 1 ? 1024 : 768;
         long blocks = 0;
         for (int i = 0; i < n; i++)
             blocks += (long)((calls[i].g->vh + kSplitSites - 1) / kSplitSites) * ((calls[i].nrhs + q - 1) / q);
+        const long slots = prec == TM_FP64 ? (q == 1 && blocks <= 4096 ? 800 : 512) : q == 1 ? 1024 : 768;
         const double t = (double)((blocks + slots - 1) / slots) * (q + 1.5);
         if (t < t_best) {
             t_best = t;

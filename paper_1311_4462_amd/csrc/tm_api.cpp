@@ -1696,9 +1696,10 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
     // reduction slots at their largest size and the odd temporaries.
     for (int i = 0; i < n; i++) {
         RedSlot rs;
-        // hop partials (one per 64-site block at most) and BLAS partials
-        // (up to kBlasMaxBlocks per rhs, two per block for a dot product)
-        const size_t need = std::max<size_t>(((pr[i].g->vh + 63) / 64) * pr[i].nrhs,
+        // hop partials (one per block of the fewest sites at most) and BLAS
+        // partials (up to kBlasMaxBlocks per rhs, two per block for a dot product)
+        constexpr uint32_t spb = split_sites(TM_FP64, 2, false);
+        const size_t need = std::max<size_t>(((pr[i].g->vh + spb - 1) / spb) * pr[i].nrhs,
                                              (size_t)2 * kBlasMaxBlocks * pr[i].nrhs);
         TM_TRY(red_slot(ctx, i, need, &rs));
         int rc = TM_OK;

@@ -450,7 +450,8 @@ HopCfg default_cfg(const HopCall *calls, int n, int prec, int nf, int twl, int r
     const bool large = working_set > (size_t)130 << 20;
     if (clv) {
         // clover epilogues: latency of the blocks' loads, whatever the rest
-        if (work <= 20000) c.bs = 64;
+        // (18-real links come in blocks of 256 only)
+        if (recon != 18 && work <= 20000) c.bs = 64;
         c.nt = (again & kAgainOut) ? 0 : kNtOut;
         return c;
     }

@@ -1,0 +1,56 @@
+"""Launch shapes outside the tuned sizes: the rule's choice for every link
+format and precision exists and gives the operator, and a tuner's file is read
+only for launches like the one it was timed on."""
+import pytest
+
+from oracle import oracle as O
+from paper_1311_4462_amd import inputs
+
+from .gpu_util import TOL, check_solve, from_native, oparams, oracle_dslash, rel, to_native
+
+pytestmark = pytest.mark.gpu
+
+CSW = 1.57
+
+
+@pytest.fixture
+def api():
+    from paper_1311_4462_amd import api as a
+    return a
+
+
+# 8, 192 and 960 sites per parity, untuned
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 4, 4, 6), (8, 6, 4, 10)])
+@pytest.mark.parametrize("flavor", [1, -1, 2])
+def test_small_clover_with_18_real_links(api, dims, flavor):
+    c = api.Context()
+    p = api.make_params(dims, 0.16, 0.13, 0.17 if flavor == 2 else 0.0, flavor, csw=CSW)
+    U = inputs.gauge_field(dims, "haar", 401)
+    op = O.with_clover(oparams(p), U, CSW)
+    g = api.Gauge(c, U, p, recon=18, precs=(0, 1))
+    a = O.project(inputs.gaussian_spinor(dims, op.nf, 402, nrhs=2), dims, 0)
+    xv = O.project(inputs.gaussian_spinor(dims, op.nf, 403, nrhs=2), dims, 1)
+    for prec in (0, 1):
+        t, tx = to_native(api, c, a, p, prec, 0, 2), to_native(api, c, xv, p, prec, 1, 2)
+        y = api.new_field(p, prec, 2)
+        for pc in (0, 1):
+            for dag in (0, 1):
+                api.tm_mat_pc(c, y, t, g, prec, pc, dag, nrhs=2)
+                got = from_native(api, c, y, p, prec, 0, 2)
+                for r in range(2):
+                    assert rel(got[r], O.mat_pc(op, U, a[r], ("asym", "sym")[pc], bool(dag))) < TOL[prec]
+        for dag, twl, epi in ((0, 0, 1), (1, 1, 2), (1, 0, 4)):
+            api.tm_dslash(c, y, t, g, prec, 1, dag, twl, epi, tx, -0.37, nrhs=2)
+            got = from_native(api, c, y, p, prec, 1, 2)
+            for r in range(2):
+                assert rel(got[r], oracle_dslash(op, U, a[r], 1, dag, twl, epi, xv[r], -0.37)) < TOL[prec]
+    tb = to_native(api, c, a, p, 0, 0, 2)
+    for inner in (0, 1):
+        x = api.new_field(p, 0, 2)
+        res = api.tm_cg(c, x, tb, g, tol=1e-10, inner=inner, nrhs=2)
+        xs = from_native(api, c, x, p, 0, 0, 2)
+        for r in range(2):
+            assert res[r]["status"] == 0
+            check_solve(op, U, xs[r], a[r], "asym", res[r]["true_rel_res_normal"])
+    g.close()
+    c.close()

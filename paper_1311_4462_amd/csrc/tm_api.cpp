@@ -2035,12 +2035,15 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
     phase.enter("tm_cg: iterations");
     int status = TM_OK;
     bool stalled = false;
-    long enqueued = 0;            // iterations enqueued (an upper bound of those run)
+    // Iterations that may have run: those of the last snapshot and the chunk in
+    // flight.  (Enqueued ones do not count: after an iteration that leaves its
+    // update to a later one, and nothing else to iterate, those between do not run.)
+    long ran = 0;
     int slot = 0;
     int in_flight = 0;            // iterations of the chunk whose snapshot is not yet read
     for (;;) {
         int launched = 0;
-        if (enqueued < par->maxiter) {
+        if (ran < par->maxiter) {
             launched = chunk;
             if (!sc.empty()) {
                 const int after = left() - in_flight;
@@ -2052,7 +2055,7 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         }
         if (launched) {
             TM_TRY(enqueue_chunk(slot, launched));
-            enqueued += launched;
+            ran += launched;
         }
         if (!in_flight) {
             // nothing to check yet
@@ -2065,6 +2068,7 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
         const int prev = slot ^ 1;
         TM_HIP(ctx, hipEventSynchronize(snap_ev[prev]));
         unpack(prev);
+        ran = hflags[3] + launched;
         if (ctx->verbose) {
             // the largest iterated residual over the rhs still iterating
             double worst = 0.0;
@@ -2107,21 +2111,17 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
                     // the chunk enqueued above was a no-op: iterate afresh
                     TM_HIP(ctx, launch_start(start, ctx->stream));
                     launched = 0;
-                    in_flight = 0;
+                    ran = hflags[3];
                 }
             }
         }
         if (done) break;
-        if (!launched) {
-            if (in_flight && enqueued >= par->maxiter) {
-                status = TM_NOT_CONVERGED;
-                break;
-            }
-            in_flight = 0;
-            continue;
+        if (!launched && ran >= par->maxiter) {
+            status = TM_NOT_CONVERGED;
+            break;
         }
         in_flight = launched;
-        slot ^= 1;
+        if (launched) slot ^= 1;
     }
     // A converged run ends on the state it has just read; otherwise the last
     // state of the device (all work enqueued so far done).

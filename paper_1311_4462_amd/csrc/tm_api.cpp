@@ -500,12 +500,16 @@ HopCfg default_cfg(const HopCall *calls, int n, int prec, int nf, int twl, int r
     return c;
 }
 
-std::string tune_key(int prec, int nf, int nr, int dagger, int twl, int epi, int recon, long vh_total,
+// Launches that share a tuned shape: one variant, as many sites x rhs, and as
+// many rhs of the problem that has most (several share the links of a block).
+// One rhs is r1, several n<count>: r2 and r4 in older files are shapes of
+// another kernel.
+std::string tune_key(int prec, int nf, int nrhs, int dagger, int twl, int epi, int recon, long vh_total,
                      bool clv)
 {
     char key[128];
-    snprintf(key, sizeof(key), "hop_p%d_f%d_r%d_d%d_t%d_e%d_c%d%s_v%ld", prec, nf, nr, dagger, twl, epi, recon,
-             clv ? "w" : "",
+    snprintf(key, sizeof(key), "hop_p%d_f%d_%c%d_d%d_t%d_e%d_c%d%s_v%ld", prec, nf, nrhs == 1 ? 'r' : 'n', nrhs,
+             dagger, twl, epi, recon, clv ? "w" : "",
              vh_total);
     return key;
 }
@@ -750,10 +754,12 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
             cand.push_back(c);
         }
     long vh_total = 0;
+    int most_rhs = 1;
     size_t wset = 0, lset = 0;
     for (int i = 0; i < n; i++) {
         const tm_gauge *g = calls[i].g;
         vh_total += (long)g->vh * calls[i].nrhs;
+        most_rhs = std::max(most_rhs, calls[i].nrhs);
         lset += 2 * gauge_parity_bytes(prec, recon, g->vh);
         wset += 3 * spinor_field_bytes(prec, g->vh, nf, calls[i].nrhs);
     }
@@ -770,7 +776,7 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
         cfg.nr = ctx->force_nr;
         if (cfg.nr > 1) cfg.bs = std::max(cfg.bs, 128);   // two rhs per thread: blocks of 128 and 256
     }
-    const std::string key = tune_key(prec, nf, nrs.back(), dagger, twl, calls[0].epi, recon, vh_total, clv);
+    const std::string key = tune_key(prec, nf, most_rhs, dagger, twl, calls[0].epi, recon, vh_total, clv);
     auto it = ctx->tuned.find(key);
     if (!cfg.split && (ctx->force_bs || ctx->force_lnt >= 0)) {
         HopCfg want{ctx->force_bs ? ctx->force_bs : cfg.bs, ctx->force_lnt >= 0 ? ctx->force_lnt != 0 : cfg.lnt,

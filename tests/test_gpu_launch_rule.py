@@ -54,3 +54,23 @@ def test_small_clover_with_18_real_links(api, dims, flavor):
             check_solve(op, U, xs[r], a[r], "asym", res[r]["true_rel_res_normal"])
     g.close()
     c.close()
+
+
+def test_tuner_tells_right_hand_sides_apart(api, monkeypatch, tmp_path):
+    """One source and two on half the lattice are launches of their own to the tuner."""
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("TM_TUNE_CACHE", str(path))
+    c = api.Context()
+    c.set_tuning(True)
+    keys = []
+    for dims, nrhs in (((4, 4, 4, 16), 1), ((4, 4, 4, 8), 2), ((4, 4, 4, 4), 4)):
+        p = api.make_params(dims, 0.16, 0.13, 0.0, 1)
+        for prec in (0, 1, 2):
+            g = api.Gauge(c, inputs.gauge_field(dims, "haar", 421), p, precs=(prec,))
+            a = O.project(inputs.gaussian_spinor(dims, 1, 422, nrhs=nrhs), dims, 0)
+            y = api.new_field(p, prec, nrhs)
+            api.tm_mat_pc(c, y, to_native(api, c, a, p, prec, 0, nrhs), g, prec, 0, 0, nrhs=nrhs)
+            g.close()
+        keys.append({line.split()[0] for line in path.read_text().splitlines()})
+    assert [len(k) for k in keys] == [6, 12, 18]
+    c.close()

@@ -750,7 +750,7 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
             if (c.ldss && !staging_fits(c.bs)) continue;
             // the direction-split kernel where it could win (see default_cfg)
             if (c.split && !may_split) continue;
-            if (ctx->force_split > 0 && !c.split) continue;
+            if (ctx->force_split > 0 && !c.split && !clv) continue;
             cand.push_back(c);
         }
     long vh_total = 0;
@@ -776,6 +776,17 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
         cfg.nr = ctx->force_nr;
         if (cfg.nr > 1) cfg.bs = std::max(cfg.bs, 128);   // two rhs per thread: blocks of 128 and 256
     }
+    // A shape from the tuner's file, or tuned for an equal key: used where its
+    // kernel exists for this launch and the environment does not ask for the other
+    auto usable = [&](const HopCfg &c) {
+        if (c.split)
+            return may_split && !clv && c.bs == kSplitThreads &&
+                   (c.nr == 1 || (nf == 1 && recon == 12 && !twl && !half && c.nr <= most_rhs));
+        for (const HopCfg &e : cand)
+            if (!e.split && c.nr == e.nr && c.bs == e.bs && c.lnt == e.lnt && c.wcap == e.wcap && c.ldss == e.ldss)
+                return true;
+        return false;
+    };
     const std::string key = tune_key(prec, nf, most_rhs, dagger, twl, calls[0].epi, recon, vh_total, clv);
     auto it = ctx->tuned.find(key);
     if (!cfg.split && (ctx->force_bs || ctx->force_lnt >= 0)) {
@@ -784,7 +795,7 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
         want.nr = cfg.nr;
         for (const HopCfg &c : cand)
             if (!c.split && c.bs == want.bs && c.lnt == want.lnt && c.wcap == 0 && c.nr == want.nr) cfg = want;
-    } else if (it != ctx->tuned.end()) {
+    } else if (it != ctx->tuned.end() && usable(cfg_decode(it->second))) {
         cfg = cfg_decode(it->second);
     } else if (ctx->tuning && cand.size() > 1 && !ctx->gate && !ctx->no_alloc) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;

@@ -74,3 +74,57 @@ def test_tuner_tells_right_hand_sides_apart(api, monkeypatch, tmp_path):
         keys.append({line.split()[0] for line in path.read_text().splitlines()})
     assert [len(k) for k in keys] == [6, 12, 18]
     c.close()
+
+
+def _key(prec, nf, rhs, twl, recon, vh_total):
+    return f"hop_p{prec}_f{nf}_{rhs}_d0_t{twl}_e0_c{recon}_v{vh_total}"
+
+
+# shapes that no kernel has: two and four rhs per thread in FP32, 18-real links
+# in blocks of 64, a group of rhs for one; bits as in the tuner's file
+@pytest.mark.parametrize("prec,recon,nrhs,rhs,code", [
+    (1, 12, 2, "r1", 256 | 1 << 18), (1, 12, 2, "r2", 256 | 1 << 18), (1, 12, 4, "r4", 256 | 2 << 18),
+    (0, 18, 1, "r1", 64), (1, 12, 1, "r1", 512 | 1 << 13 | 4 << 20), (1, 18, 2, "n2", 512 | 1 << 13 | 2 << 20),
+    (1, 12, 2, "n2", 256 | 1 << 18)])
+def test_entry_of_another_launch_is_not_used(api, prec, recon, nrhs, rhs, code, monkeypatch, tmp_path):
+    dims = (4, 4, 4, 4)
+    p = api.make_params(dims, 0.16, 0.13, 0.0, 1)
+    path = tmp_path / "tune.txt"
+    path.write_text(f"{_key(prec, 1, rhs, 0, recon, 128 * nrhs)} {code}\n")
+    monkeypatch.setenv("TM_TUNE_CACHE", str(path))
+    c = api.Context()
+    U = inputs.gauge_field(dims, "haar", 431)
+    g = api.Gauge(c, U, p, recon=recon, precs=(prec,))
+    a = O.project(inputs.gaussian_spinor(dims, 1, 432, nrhs=nrhs), dims, 1)
+    y = api.new_field(p, prec, nrhs)
+    api.tm_dslash(c, y, to_native(api, c, a, p, prec, 1, nrhs), g, prec, 0, nrhs=nrhs)
+    got = from_native(api, c, y, p, prec, 0, nrhs)
+    for r in range(nrhs):
+        assert rel(got[r], oracle_dslash(oparams(p), U, a[r], 0, 0, 0, 0, None, 0.0)) < TOL[prec]
+    g.close()
+    c.close()
+
+
+@pytest.mark.parametrize("split", ["0", "1"])
+def test_forced_kernel_overrides_the_tuner_file(api, split, monkeypatch, tmp_path):
+    """TM_HOP_SPLIT holds whatever the file says; the two kernels round the
+    twist on load differently, so the bits of a hop tell which one ran."""
+    dims = (6, 4, 4, 6)
+    p = api.make_params(dims, 0.16, 0.13, 0.0, 1)
+    U = inputs.gauge_field(dims, "haar", 441)
+    a = O.project(inputs.gaussian_spinor(dims, 1, 442), dims, 1)
+    path = tmp_path / "tune.txt"
+    bits = []
+    for forced, code in (("0", None), ("1", None), (split, (512 | 1 << 13, 256 | 1 << 16)[int(split)])):
+        if code is not None:
+            path.write_text(f"{_key(0, 1, 'r1', 1, 12, 288)} {code}\n")
+            monkeypatch.setenv("TM_TUNE_CACHE", str(path))
+        monkeypatch.setenv("TM_HOP_SPLIT", forced)
+        c = api.Context()
+        g = api.Gauge(c, U, p, precs=(0,))
+        y = api.new_field(p, 0)
+        api.tm_dslash(c, y, to_native(api, c, a, p, 0, 1), g, 0, 0, 0, 1)
+        bits.append(from_native(api, c, y, p, 0, 0).tobytes())
+        g.close()
+        c.close()
+    assert bits[0] != bits[1] and bits[2] == bits[int(split)]

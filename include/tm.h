@@ -128,16 +128,22 @@ typedef struct {
     int maxiter;          /* iteration cap (inner iterations for mixed)         */
     int outer;            /* precision of x and b: TM_FP64                      */
     int inner;            /* TM_FP64 (plain CG) or TM_FP32 / FP16 / BF16 (mixed) */
-    double delta;         /* reliable-update threshold (mixed); 0: 0.01 (FP16), 0.02 (BF16), 0.001 (FP32);
-                             raised to 2e-3 (FP16), 1e-2 (BF16), 1e-5 (FP32) at least */
+    double delta;         /* reliable-update threshold (mixed): the update follows the
+                             iteration whose |r| is below delta times the largest
+                             since the last update.  0: 0.01 (FP16), 0.02 (BF16),
+                             0.001 (FP32), and the update may follow one (FP16) or up
+                             to three (FP32) iterations later.  Raised to 2e-3 (FP16),
+                             1e-2 (BF16), 1e-5 (FP32) at least                   */
     int use_x0;           /* 1: x holds the initial guess                       */
     int nrhs;             /* right-hand sides solved together (>= 1)            */
     int graph_iters;      /* > 0: capture this many iterations in a hipGraph    */
     int check_every;      /* iterations between host convergence checks (eager
                              solves; 0 -> 8).  Every iteration is gated on the
                              device by the convergence state, so iterations
-                             enqueued after convergence do nothing and the
-                             iteration count is exact for any period.        */
+                             enqueued after convergence do nothing.  The period
+                             does not change the course of a solve, except where
+                             delta is 0 (mixed FP32 / FP16): an update that is due
+                             comes at the latest with the end of a period or graph. */
     int solution;         /* tm_solution                                        */
     double stall_factor;  /* mixed: a reliable update whose true |r| is not
                              below stall_factor times the |r| of the previous

@@ -1940,8 +1940,9 @@ int cg_run(tm_ctx *ctx, std::vector<CGProblem> &pr, const tm_cg_params *par, tm_
     // 12030 / 11680 / 11530).  FP16 loses some from the third on (32^3 x 64
     // doublet, kappa 0.15: 170 iterations, 170, 182, 187; 120.3 ms, 119.1,
     // 126.2, 128.9), BF16 from the second (12^3 x 24, kappa 0.15: 104, 116,
-    // 115, 156).
-    const int update_every = inner == TM_FP32 ? 4 : inner == TM_FP16 ? 2 : 1;
+    // 115, 156).  With a threshold of the caller's they follow each, so that
+    // the update comes where the threshold says.
+    const int update_every = par->delta > 0 ? 1 : inner == TM_FP32 ? 4 : inner == TM_FP16 ? 2 : 1;
     auto iteration = [&](int k, int count) -> int {
         const bool upd = k % update_every == update_every - 1 || k == count - 1;
         ctx->post = start.post;

@@ -64,3 +64,20 @@ def test_unconverged_solve_ran_all_it_may(api, inner, every):
             assert r["status"] == 0 or r["iters"] == m, (tol, m, r)
     g.close()
     c.close()
+
+
+@pytest.mark.parametrize("inner", [1, 2, 3])
+def test_given_delta_places_the_updates(api, inner):
+    """With a threshold of the caller's the reliable updates follow the
+    iteration that reaches it: the same course under any host period."""
+    import torch
+    c, g, b, x = _mixed(api, inner)
+    runs = []
+    for kw in (dict(check_every=1), dict(check_every=3), dict(), dict(graph_iters=5)):
+        r = api.tm_cg(c, x, b, g, tol=1e-10, inner=inner, delta=0.05, **kw)[0]
+        assert r["status"] == 0
+        runs.append((r["iters"], r["reliable_updates"], x.clone()))
+    for it, up, v in runs[1:]:
+        assert (it, up) == runs[0][:2] and torch.equal(v, runs[0][2])
+    g.close()
+    c.close()

@@ -923,9 +923,10 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
     // us), with more blocks as long as the finish launch.  Mixed solves, whose
     // 13 launches an iteration the host enqueues no faster than they run, gain
     // by the launch itself (16^3 x 32 FP32 4290 -> 3880 us, 12^3 x 24 FP16
-    // 3310 -> 3000; FP64 CG of the doublet at 16^3 x 32 9690 -> 9950).
+    // 3310 -> 3000; FP64 CG of the doublet at 16^3 x 32 9690 -> 9950).  The
+    // variants with twist on load have no finish.
     B.post = ctx->post;
-    B.finish_here = cfg.split && calls[0].fin != FIN_NONE && ctx->post.flags &&
+    B.finish_here = cfg.split && !twl && calls[0].fin != FIN_NONE && ctx->post.flags &&
                     B.total_blocks <= (ctx->post.mixed ? kFinishGroup * kFinishGroups : kFinishGroup);
     B.gate_copy = ctx->gate_copy;
     TM_HIP(ctx, dispatch_hop(B, prec, nf, cfg.nr, dagger, twl, recon, cfg, clv, lds, ctx->stream));

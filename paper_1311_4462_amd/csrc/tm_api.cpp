@@ -1149,7 +1149,7 @@ int tm_ctx_create(tm_ctx **ctx, void *hip_stream)
     e = getenv("TM_HOP_LDS");
     if (e) c->force_ldss = atoi(e) ? 1 : 0;
     e = getenv("TM_HOP_NR");
-    if (e) c->force_nr = atoi(e);
+    if (e) c->force_nr = std::max(0, atoi(e));
     e = getenv("TM_HOP_NT");
     if (e) c->force_nt = atoi(e) & 7;
     e = getenv("TM_HOP_SPLIT");

@@ -128,3 +128,22 @@ def test_forced_kernel_overrides_the_tuner_file(api, split, monkeypatch, tmp_pat
         g.close()
         c.close()
     assert bits[0] != bits[1] and bits[2] == bits[int(split)]
+
+
+@pytest.mark.parametrize("nr", ["-1", "-3", "0", "99"])
+def test_group_outside_its_range(api, nr, monkeypatch):
+    monkeypatch.setenv("TM_HOP_SPLIT", "1")
+    monkeypatch.setenv("TM_HOP_NR", nr)
+    dims, nrhs = (4, 4, 4, 6), 3
+    c = api.Context()
+    p = api.make_params(dims, 0.16, 0.13, 0.0, 1)
+    U = inputs.gauge_field(dims, "haar", 451)
+    g = api.Gauge(c, U, p, precs=(0,))
+    a = O.project(inputs.gaussian_spinor(dims, 1, 452, nrhs=nrhs), dims, 1)
+    y = api.new_field(p, 0, nrhs)
+    api.tm_dslash(c, y, to_native(api, c, a, p, 0, 1, nrhs), g, 0, 0, nrhs=nrhs)
+    got = from_native(api, c, y, p, 0, 0, nrhs)
+    for r in range(nrhs):
+        assert rel(got[r], oracle_dslash(oparams(p), U, a[r], 0, 0, 0, 0, None, 0.0)) < TOL[0]
+    g.close()
+    c.close()

@@ -1037,13 +1037,11 @@ struct FastDiv {
 
 struct HopProblem {
     int X[4];            // Lx, Ly, Lz, Lt
-    FastDiv dx, dy, dz;  // by Lx / 2, Ly, Lz
     int vh;              // sites per parity
     int nrhs;
     int blk_start;       // first logical block of this problem
     int nsb;             // site blocks
     int ngrp;            // rhs groups
-    int nrg;             // rhs per group
     int out_parity;
     int zc;              // z-planes per brick of the processing order (0: lexicographic)
     int ts;              // time slices per slab of the processing order (zc > 0)
@@ -1056,23 +1054,34 @@ struct HopProblem {
     // nullable: CG residual update in the epilogue, out = out - alpha A with
     // A the epilogue's result and alpha of each rhs read from here
     const CGScalars *upd;
-    SpinorPtr res;       // HopBatch::res_prec >= 0: out = res - A, out in that precision
     Reduce red;
+    // used by the direction-split kernel and by RES variants only
+    FastDiv dx, dy, dz;  // by Lx / 2, Ly, Lz
+    int nrg;             // rhs per group
+    SpinorPtr res;       // HopBatch::res_prec >= 0: out = res - A, out in that precision
 };
+
+// The arguments of a launch come from memory no cache holds yet, a line of 64
+// bytes at a time: what every variant reads of a launch of one problem (the
+// head and the front of p[0]) is kept to the first four.  With the other
+// members in between it took six, and a small launch 0.2-0.5 us more (twisted
+// clover at 6^3 x 8, FP32 16.3 -> 15.7 us, FP64 19.2 -> 18.4; FP64 doublet at
+// 12^3 x 24 20.2 -> 19.5).
 
 struct HopBatch {
     int nprob;
     int total_blocks;
     const int *gate;     // nullable: skip the launch when *gate == 0
     int *gate_copy;      // nullable: receives *gate (the first launch of a CG iteration)
-    CGPost post;         // with finish_here
     int finish_here;     // the last block finishes the reductions (direction-split kernel)
     int epi;             // tm_epilogue
     int res_prec;        // precision of a true residual's output, < 0: none (RES variants)
     int xcd_remap;       // 1: give every XCD a contiguous range of blocks
     int nt_streams;      // kNtOut | kNtX | kNtTime: streams accessed non-temporally
     HopProblem p[kMaxProblems];
+    CGPost post;         // with finish_here
 };
+static_assert(offsetof(HopBatch, p) + offsetof(HopProblem, dx) <= 256, "the first four lines");
 
 // Map hardware workgroup id to a logical block so that each of the 8 XCDs
 // (which receive workgroups round-robin) gets one contiguous range.

@@ -392,11 +392,16 @@ std::vector<HopCfg> cfg_candidates(int prec, int nf, int nr, int twl, int recon,
 // Right-hand sides per block of the direction-split kernel (FP32 / FP64, one
 // flavour, 12-real links): the links are loaded once per block, so more is
 // better until the blocks no longer fill the chip evenly.  `slots` blocks run
-// at once (three per compute unit in FP32, four of the single-rhs kernel with
-// its one LDS buffer, two in FP64; FP64 with one rhs behaves like three while
-// the launch is small and its links stay in L2); a block's time is about its
-// rhs and 1.5 more for the links and the start, and the launch takes the
-// rounds its blocks need.  16^3 x 32 FP32, 12 rhs, R^-1 D: 1 / 2 / 3 / 4 / 6 /
+// at once (three per compute unit in FP32, two in FP64); a block's time is about
+// its rhs and 1.5 more for the links and the start, and the launch takes the
+// rounds its blocks need.  The blocks of one rhs are short and have one LDS
+// buffer, so they overlap and no round is left half empty: their launches grow
+// evenly, as with 1100 (FP32) or 768 (FP64) at once (M^, FP32 972 / 1944 /
+// 3000 / 6000 blocks 14.6 / 22.2 / 33.4 / 60.5 us; FP64 972 / 1944 / 3840 blocks
+// 23.4 / 40.1 / 72.5 us; 16^3 x 32 FP32 with six rhs by 1 / 2 / 3 / 6 59.2 / 57.6
+// / 56.9 / 62.8, 12^3 x 24 22.2 / 26.1 / 22.6 / 32.5, FP64 with three by 1 / 3
+// 23.4 / 28.3).  In FP64 that holds while the links of all blocks stay in L2;
+// beyond 4096 blocks each takes its turn.  16^3 x 32 FP32, 12 rhs, R^-1 D: 1 / 2 / 3 / 4 / 6 /
 // 12 per block 65 / 57 / 54 / 51 / 49 / 53 us (four per thread of the
 // one-thread kernel: 90).  FP64 CG, us: 12^3 x 24 with four rhs 2305 / 2398 /
 // 2866 / 2508 by 1 / 2 / 3 / 4, 16^3 x 32 5548 / 5305 / 6312 / 5117, with
@@ -410,8 +415,10 @@ int split_group(const HopCall *calls, int n, int prec)
         long blocks = 0;
         for (int i = 0; i < n; i++)
             blocks += (long)((calls[i].g->vh + kSplitSites - 1) / kSplitSites) * ((calls[i].nrhs + q - 1) / q);
-        const long slots = prec == TM_FP64 ? (q == 1 && blocks <= 4096 ? 800 : 512) : q == 1 ? 1024 : 768;
-        const double t = (double)((blocks + slots - 1) / slots) * (q + 1.5);
+        const long slots = prec == TM_FP64 ? 512 : 768;
+        const double t = q > 1 || (prec == TM_FP64 && blocks > 4096)
+                             ? (double)((blocks + slots - 1) / slots) * (q + 1.5)
+                             : 2.5 * (double)blocks / (prec == TM_FP64 ? 768 : 1100);
         if (t < t_best) {
             t_best = t;
             best = q;
@@ -450,8 +457,11 @@ HopCfg default_cfg(const HopCall *calls, int n, int prec, int nf, int twl, int r
     const bool large = working_set > (size_t)130 << 20;
     if (clv) {
         // clover epilogues: latency of the blocks' loads, whatever the rest
-        // (18-real links come in blocks of 256 only)
-        if (recon != 18 && work <= 20000) c.bs = 64;
+        // (18-real links come in blocks of 256 only).  M^ by 64 / 256: FP64
+        // 6^3 x 8 19.2 / 21.1, 8^3 x 16 17.6 / 20.4; FP32 doublet 8^3 x 16
+        // 22.5 / 23.5, but of some 16 waves those of a block share the
+        // fetches of the code: 6^3 x 8 25.0 / 24.4, 4^4 22.0 / 21.6
+        if (recon != 18 && work <= 20000 && (prec == TM_FP64 || work > 1024)) c.bs = 64;
         c.nt = (again & kAgainOut) ? 0 : kNtOut;
         return c;
     }
@@ -471,7 +481,14 @@ HopCfg default_cfg(const HopCall *calls, int n, int prec, int nf, int twl, int r
     const bool shared = nrhs > 1 && nf == 1 && recon == 12 && !twl && !half;   // several rhs per block
     const bool fits = half ? work <= (nf == 2 ? 65536 : 100000)
                      : prec == TM_FP32 ? nf == 1 || work * nf <= 1L << 20 : shared || work <= (nf == 1 ? 250000 : twl ? 500000 : 900000);
-    if (may_split + (int)fits >= 2) {
+    // An FP64 doublet whose blocks of 256 give nearly every compute unit one,
+    // all in one round, where the split kernel's two-flavour blocks of 32
+    // take three and more: M^ one-thread / split, us, 46080 sites x rhs 35.6 /
+    // 35.7, 49152 35.9 / 36.9, 59904 38.7 / 42.3, 62208 38.8 / 42.2, but from
+    // 250 blocks on some unit gets a second, 64512 47.1 / 44.4, 65536 62.2 / 47.5.
+    // (R^-1 on load: 52.3 / 45.7 over the two launches at 62208.)
+    const bool one_round = prec == TM_FP64 && nf == 2 && !twl && work > 47000 && work <= 62500;
+    if (may_split + (int)(fits && !one_round) >= 2) {
         c.bs = kSplitThreads;
         c.split = true;
         if (shared) c.nr = group ? group : split_group(calls, n, prec);

@@ -147,3 +147,49 @@ def test_group_outside_its_range(api, nr, monkeypatch):
         assert rel(got[r], oracle_dslash(oparams(p), U, a[r], 0, 0, 0, 0, None, 0.0)) < TOL[0]
     g.close()
     c.close()
+
+
+# (lattice, flavours, precision, clover): sites on either side of the lines of the
+# rule, 16-bit, FP32 and FP64
+LINES = [((16, 16, 16, 32), 2, 2, 0), ((16, 16, 16, 36), 2, 2, 0), ((16, 16, 16, 36), 2, 3, 0),
+         ((16, 16, 20, 36), 1, 2, 0), ((16, 20, 20, 32), 1, 3, 0),
+         ((24, 24, 32, 56), 2, 1, 0), ((28, 28, 28, 48), 2, 1, 0),
+         ((20, 20, 20, 60), 1, 0, 0), ((20, 20, 24, 56), 1, 0, 0),
+         ((12, 16, 16, 28), 2, 0, 0), ((16, 16, 16, 24), 2, 0, 0), ((12, 16, 16, 40), 2, 0, 0),
+         ((16, 16, 16, 32), 2, 0, 0), ((24, 24, 24, 72), 2, 0, 0), ((28, 28, 28, 48), 2, 0, 0),
+         ((28, 28, 32, 64), 2, 0, 0), ((32, 32, 32, 60), 2, 0, 0),
+         ((4, 4, 8, 8), 2, 1, 1), ((8, 8, 8, 8), 1, 1, 1), ((12, 12, 12, 20), 1, 0, 1), ((16, 16, 16, 12), 2, 0, 1)]
+
+
+@pytest.mark.parametrize("recon", [12, 18, 8])
+@pytest.mark.parametrize("dims,nf,prec,clover", LINES)
+def test_rule_on_both_sides_of_its_lines(api, dims, nf, prec, clover, recon, monkeypatch):
+    """The unforced launch and both forced kernels give the same operator (equal
+    but for the rounding of the twist on load)."""
+    import torch
+    if clover and recon == 8:
+        pytest.skip("no clover with 8-real links")
+    p = api.make_params(dims, 0.16, 0.13, 0.17 if nf == 2 else 0.0, nf, csw=CSW * clover)
+    small = torch.from_numpy(inputs.gauge_field((4, 4, 4, 4), "haar", 461)).cuda()
+    U = small.repeat(1, *(n // 4 for n in dims[::-1]), 1, 1)
+    gen = torch.Generator(device="cuda").manual_seed(462)
+    a = torch.randn((1, *dims[::-1], nf, 4, 3), dtype=torch.complex128, device="cuda", generator=gen)
+    outs = []
+    for split in (None, "0", "1"):
+        if split is not None:
+            monkeypatch.setenv("TM_HOP_SPLIT", split)
+        c = api.Context()
+        g = api.Gauge(c, U, p, recon=recon, precs=(prec,))
+        t = api.tm_spinor_pack(c, a, p, prec, 0, 1)
+        for pc in (0, 1):
+            for dag in (0, 1):
+                y = api.new_field(p, prec)
+                api.tm_mat_pc(c, y, t, g, prec, pc, dag)
+                outs.append(api.tm_spinor_unpack(c, y, p, prec, 0, 1))
+        g.close()
+        c.close()
+    for k in range(4):
+        n = outs[k].norm().item()
+        assert 0 < n < float("inf")
+        for o in (outs[4 + k], outs[8 + k]):
+            assert (o - outs[k]).norm().item() < (1e-14, 1e-6, 1e-3, 8e-3)[prec] * n

@@ -396,16 +396,17 @@ std::vector<HopCfg> cfg_candidates(int prec, int nf, int nr, int twl, int recon,
 // its rhs and 1.5 more for the links and the start, and the launch takes the
 // rounds its blocks need.  The blocks of one rhs are short and have one LDS
 // buffer, so they overlap and no round is left half empty: their launches grow
-// evenly, as with 1100 (FP32) or 768 (FP64) at once (M^, FP32 972 / 1944 /
-// 3000 / 6000 blocks 14.6 / 22.2 / 33.4 / 60.5 us; FP64 972 / 1944 / 3840 blocks
-// 23.4 / 40.1 / 72.5 us; 16^3 x 32 FP32 with six rhs by 1 / 2 / 3 / 6 59.2 / 57.6
-// / 56.9 / 62.8, 12^3 x 24 22.2 / 26.1 / 22.6 / 32.5, FP64 with three by 1 / 3
-// 23.4 / 28.3).  In FP64 that holds while the links of all blocks stay in L2;
-// beyond 4096 blocks each takes its turn.  16^3 x 32 FP32, 12 rhs, R^-1 D: 1 / 2 / 3 / 4 / 6 /
-// 12 per block 65 / 57 / 54 / 51 / 49 / 53 us (four per thread of the
-// one-thread kernel: 90).  FP64 CG, us: 12^3 x 24 with four rhs 2305 / 2398 /
-// 2866 / 2508 by 1 / 2 / 3 / 4, 16^3 x 32 5548 / 5305 / 6312 / 5117, with
-// twelve 17270 by 1, 14500 by 6 and 13900 by 12.
+// evenly, in the same unit by 2.27 (FP32) or, from 1.1, 2.8 (FP64) for 1000
+// blocks.  In FP64 that holds while the links of all blocks stay in L2; beyond
+// 4096 blocks each takes its turn.  M^, us: one rhs per block, FP32 972 / 1944 /
+// 3000 / 6000 blocks 14.6 / 22.2 / 33.4 / 60.5, FP64 864 / 972 / 1944 / 3840
+// blocks 21.2 / 23.4 / 40.1 / 72.5; 16^3 x 32 FP32 with six rhs by 1 / 2 / 3 / 6
+// 59.2 / 57.6 / 56.9 / 62.8, 12^3 x 24 22.2 / 26.1 / 22.6 / 32.5; 12^3 x 24 FP64
+// with three by 1 / 3 23.4 / 28.3, 8^2 x 12 x 24 with six by 1 / 2 21.2 / 20.5.
+// R^-1 D of 16^3 x 32 FP32, 12 rhs, by 1 / 2 / 3 / 4 / 6 / 12 65 / 57 / 54 / 51 /
+// 49 / 53 us (four per thread of the one-thread kernel: 90).  FP64 CG, us:
+// 12^3 x 24 with four rhs 2305 / 2398 / 2866 / 2508 by 1 / 2 / 3 / 4, 16^3 x 32
+// 5548 / 5305 / 6312 / 5117, with twelve 17270 by 1, 14500 by 6 and 13900 by 12.
 int split_group(const HopCall *calls, int n, int prec)
 {
     int most = 1, best = 1;
@@ -418,7 +419,8 @@ int split_group(const HopCall *calls, int n, int prec)
         const long slots = prec == TM_FP64 ? 512 : 768;
         const double t = q > 1 || (prec == TM_FP64 && blocks > 4096)
                              ? (double)((blocks + slots - 1) / slots) * (q + 1.5)
-                             : 2.5 * (double)blocks / (prec == TM_FP64 ? 768 : 1100);
+                         : prec == TM_FP64 ? 1.1 + 0.0028 * (double)blocks
+                                           : 0.00227 * (double)blocks;
         if (t < t_best) {
             t_best = t;
             best = q;

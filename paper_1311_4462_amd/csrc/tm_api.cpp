@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -302,7 +303,7 @@ struct HopCfg {
 // (its rhs per block in the wave-cap field)
 int cfg_code(const HopCfg &c)
 {
-    const int l2nr = c.split ? 0 : c.nr == 4 ? 2 : c.nr == 2 ? 1 : 0;
+    const int l2nr = !c.split && c.nr == 2 ? 1 : 0;
     return c.bs | ((c.nt & 7) << 10) | (c.split ? 1 << 13 : 0) | (c.lnt ? 1 << 16 : 0) | (c.ldss ? 1 << 17 : 0) |
            (l2nr << 18) | ((c.split ? c.nr : c.wcap) << 20) | (c.zc << 24);
 }
@@ -786,11 +787,10 @@ int launch_hops(tm_ctx *ctx, const HopCall *calls, int n)
     HopCfg cfg = default_cfg(calls, n, prec, nf, twl, recon, clv, lset, wset,
                              may_split, std::min(ctx->force_nr, 12));
     if (ctx->tuning && cfg.split && cfg.nr > 1)
-        for (int q : {2, 4, cfg.nr})
-            if (q <= cfg.nr) {
-                cand.push_back(cfg);
-                cand.back().nr = q;
-            }
+        for (int q : std::set<int>{std::min(2, cfg.nr), std::min(4, cfg.nr), cfg.nr}) {
+            cand.push_back(cfg);
+            cand.back().nr = q;
+        }
     if (!cfg.split && std::find(nrs.begin(), nrs.end(), ctx->force_nr) != nrs.end()) {
         cfg.nr = ctx->force_nr;
         if (cfg.nr > 1) cfg.bs = std::max(cfg.bs, 128);   // two rhs per thread: blocks of 128 and 256

@@ -61,7 +61,7 @@ struct SplitLds {
 };
 
 // Waves per SIMD the register allocation is held to (a block is two).
-template <int P, int NF, bool TWL, bool MR>
+template <int P, int NF, bool TWL>
 constexpr int split_waves()
 {
     return P == TM_FP64 && (split_nl<P, NF, TWL>() == 2 || TWL) ? 2 : 4;
@@ -277,7 +277,7 @@ __device__ __forceinline__ void split_finish(const HopBatch &B)
 // becomes the true residual pb.res - A, rounded to precision B.res_prec on its
 // way out; the norm is that of the FP64 values.
 template <int P, int NF, bool DAG, bool TWL, int RECON, bool LNT, bool MR, bool RES = false>
-__global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())) hop_split_kernel(const HopBatch B)
+__global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL>())) hop_split_kernel(const HopBatch B)
 {
     using real = typename Prec<P>::real;
     using Lds = SplitLds<P, NF, TWL, RES>;
@@ -333,9 +333,9 @@ __global__ void __launch_bounds__(kSplitThreads, (split_waves<P, NF, TWL, MR>())
     // two of a chunk and a wave's stores stay contiguous.
     int k, site;
     if constexpr (P == TM_FP32) {
+        static_assert(NL == NF, "the flavours of a wave's halves come by whole elements");
         k = (int)(threadIdx.x >> 7) * 2 + (int)(threadIdx.x & 1);
-        site = NL == NF ? (int)(threadIdx.x & 127) >> 1
-                        : (lane & 32) | (int)(threadIdx.x & 64) >> 2 | (lane & 31) >> 1;
+        site = (int)(threadIdx.x & 127) >> 1;
     } else {
         k = wave;
         site = lane;

@@ -832,10 +832,12 @@ struct CGScalars {
 enum FinOp { FIN_NONE = 0, FIN_STORE = 1, FIN_ALPHA = 2, FIN_BETA = 3, FIN_STORE_RR = 4, FIN_RELIABLE = 5 };
 
 // Two-stage deterministic reduction: every block of the producing kernel
-// stores its partial sum per vector; a separate one-block finish kernel adds
-// the partials in a fixed order and applies the finishing operation.  (No
-// atomics and no device-scope fences in the producing kernel: on a multi-XCD
-// part each such fence writes back the XCD's L2.)
+// leaves its partial sum per vector, and the partials are added in a fixed
+// order before the finishing operation.  A separate finish launch does that, so
+// that the producing kernel needs no device-scope fence (on a multi-XCD part
+// each writes back the XCD's L2); or, in a small launch of the direction-split
+// kernel in a solve, its last block, with partials exchanged and loaded at
+// device scope past the L2s and blocks counted by atomics (split_finish).
 struct Reduce {
     double *partials;      // [nvec][nblk]
     double *out;           // FIN_STORE destination [nvec]

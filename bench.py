@@ -40,7 +40,7 @@ BYTES_PER_REAL = {0: 8, 1: 4, 2: 2, 3: 2}     # FP64, FP32, FP16, BF16
 HEADLINE_DIMS = (32, 32, 32, 64)
 HEADLINE = dict(kappa=0.1615, mu=0.15, eps=0.19)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hop_traffic.json")
-HOP_SOURCES = ("tm_hop.inc.h", "tm_impl.h", "tm_hop_fp32.hip")
+HOP_SOURCES = ("tm_hop.inc.h", "tm_hop_split.inc.h", "tm_impl.h", "tm_hop_fp32.hip", "tm_hop_split_fp32.hip")
 
 
 def log(*a):

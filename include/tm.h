@@ -347,7 +347,10 @@ int tm_force(tm_ctx *ctx, void *F_dev, int force_prec, const void *X_e, const tm
  * single-use streams (output stores; with the xpay operand and / or the
  * time-neighbour loads) accessed non-temporally -- cached per context and
  * persisted to $TM_TUNE_CACHE if set; 0 disables (a rule on sizes and
- * precision is then used).
+ * precision is then used).  An entry holds for launches of its variant, total
+ * sites x right-hand sides and number of right-hand sides; one whose kernel
+ * does not exist for a launch, or that the variables below rule out, is not
+ * used.
  * Read at context creation, for experiments: TM_HOP_SPLIT (1 / 0: the
  * direction-split kernel wherever it exists / nowhere), TM_HOP_NR, TM_HOP_BS,
  * TM_LINK_NT, TM_HOP_WCAP, TM_HOP_ZC, TM_HOP_LDS, TM_HOP_NT (mask: 1 output,

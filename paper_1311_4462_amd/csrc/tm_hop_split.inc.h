@@ -17,7 +17,7 @@
 namespace twm {
 
 // Flavours per thread.  FP64 doublets put the two flavours of 32 sites into the
-// halves of a wave (both load the same link), so a block takes the LDS (51 KiB)
+// halves of a wave (both load the same link), so a block takes the LDS (52 KiB)
 // and the registers of the one-flavour kernel and two blocks share a compute
 // unit where one did: R^-1 D of 12^3 x 24 in a solve 9.5 us against 13.2 with
 // both flavours of 64 sites in a thread, 24^3 x 48 126 against 139.  In FP32,
@@ -67,7 +67,7 @@ constexpr int split_waves()
     return P == TM_FP64 && (split_nl<P, NF, TWL>() == 2 || TWL) ? 2 : 4;
 }
 // Several rhs: two LDS buffers where they leave room for two blocks per
-// compute unit (FP64's take 51 KiB each), else one and a second barrier per
+// compute unit (FP64's take 52 KiB each), else one and a second barrier per
 // rhs.
 template <int P>
 constexpr bool split_two_buffers()
